@@ -10,22 +10,28 @@
 // Outputs at padding positions are computed and discarded (2 (H + W + 2) of
 // every (H + 2)(W + 2) positions).
 // One 512-thread workgroup per CU owns a contiguous range of positions
-// [P0, P1).
+// [P0, P1) and walks it in tiles of TR rows (64; 128 where one wave covers
+// all channels of a row).
 //   * Weights: each of the 8 waves owns a 32-channel slice of the GEMM K
 //     (input channels) and a 32-column slice of the outputs, and keeps the
 //     matrix-core fragments of that slice for all nine taps in registers
-//     (72 VGPRs), loaded once through LDS from [kh][kw][ci][co] (transposed for
-//     the forward GEMM, taps flipped for the data gradient).  The remaining
-//     8 / (K slices x N slices) waves split the 128 rows of a tile.
-//   * Inputs: a ring buffer of position rows in LDS.  A 128-row output tile
-//     at p0 needs the rows [p0 - (W+3), p0 + 128 + W + 3); consecutive tiles
-//     share all but 128 of them, so each input pixel is read from HBM and
-//     transformed by the prologue once (no halo re-reads inside a workgroup);
-//     padding positions are written as zeros.
-// The 128 new rows of the next tile are loaded into registers while the
-// matrix cores work on the current tile, together with the epilogue operand
-// of the current tile.  Two waves per SIMD let one wave's prologue / epilogue
-// arithmetic overlap the other's matrix-core work.  Zero padding applies to
+//     (72 VGPRs).  The data gradient's [n][k] rows are fragments as they lie in
+//     memory; the forward's [k][n] rows are copied to LDS as they are and
+//     read by transposing reads.  The remaining 8 / (K slices x N slices)
+//     waves split the rows of a tile.
+//   * Inputs: a ring buffer of position rows in LDS: the window of the current
+//     tile, [p0 - (W+3), p0 + TR + W + 3), and the TR rows the next one adds,
+//     so each input pixel is read from HBM and transformed by the prologue
+//     once (no halo re-reads inside a workgroup); padding positions are
+//     written as zeros.
+// One barrier per tile.  Between two barriers the matrix cores work on tile t
+// (partial tiles of the K slices to one of two float32 buffers in LDS), the
+// epilogue runs on tile t - 1 (the other buffer) and the rows of tile t + 1
+// are transformed into the ring; none of the three depends on another.  Half
+// of the waves (one of the two of each SIMD) run the matrix-core part first,
+// the other half last, so a SIMD's matrix cores and its vector units are busy
+// at the same time.  Global loads (ring rows and epilogue operands) go to U
+// register sets and stay in flight for U - 1 tiles.  Zero padding applies to
 // the CONV input, i.e. after BN and ReLU.  The float32 partial tiles of the K
 // slices are added in LDS in a fixed order.
 //
@@ -33,6 +39,18 @@
 // global access is coalesced, and keeps the per-channel statistics of the
 // workgroup's rows in registers: one partial row per workgroup.  Prologue /
 // epilogue modes are those of conv_rows.hip.
+//
+// What bounds it: instructions issued per wave, not HBM (loading the same
+// rows over and over saved 3 of 46 us).  Two phases per 128-row tile with a
+// position decode per row and a ring wrap per fragment took 840 instructions
+// per wave and phase pair, half of them scalar; the walkers (p3_step) and one
+// address per filter row leave about 350.  128 -> 32 channels forward on
+// 64 images of 56 x 56: 40.2 -> 31 us; its data gradient with the BN-backward
+// epilogue: 51 -> 39 us (HBM floor 23); 64 -> 64 channels, 128 images,
+// forward: 73 -> 52 us.  Slower: 768 threads (three waves per SIMD), 8-byte
+// vectors so that every wave holds rows of each part, all three parts in one
+// basic block with the matrix-core work interleaved (34.6, 36, 36-39 us
+// against 33.5, by HIP events).
 #include "common.hpp"
 #include "kernels.hpp"
 #include "mfma.hpp"
@@ -42,40 +60,45 @@
 namespace bnr {
 
 constexpr int kP3Threads = 512;
-constexpr int kP3BM = 128;          // output rows per tile
-constexpr int kP3MaxW = 61;         // widest image row (ring = 128 + 2 (W + 3) rows: fill = two batches)
-constexpr int kP3MaxH = 896;        // tallest image (exact multiply-shift row quotients)
+constexpr int kP3MaxW = 61;         // widest image row (2 (W + 3) halo rows in kP3Fill batches less one tile)
+constexpr int kP3MaxH = 896;        // tallest image
 
-// LDS layout (bytes): [ring: ring rows, then copies of its first 16 rows (so
-// a 16-row fragment starting anywhere in the ring is contiguous), then one
-// junk row for masked writes; lda bf16 per row]
-// [stage: weights Ws[9][NP][ldw] bf16 at the start; afterwards the float32
-// K-slice partial tiles red[WK][128][ldr] and finally the statistics scratch]
+// Rows of a tile with wk x wn channel slices (every wave has at least 16), the
+// ring batches (of one tile's rows) that cover a tile's window, the ring rows
+// (one batch more: the one being written while the window is read), and the
+// ring rows copied past its end, so that the rows a wave reads for one filter
+// row of a tile are contiguous wherever they start.
+constexpr int p3_tile_rows(int wk, int wn) { return wk * wn >= 2 ? 64 : 128; }
+constexpr int p3_fill(int tr) { return (tr + 2 * (kP3MaxW + 3) + tr - 1) / tr; }
+constexpr int p3_ring(int tr) { return (p3_fill(tr) + 1) * tr; }
+constexpr int p3_copies(int wk, int wn) { return p3_tile_rows(wk, wn) * wk * wn / 8 + 2; }
+
+// LDS layout (bytes): [ring: ring rows, then the copies; lda bf16 per row]
+// [stage: the forward's weights Ws[9][KP][NP] bf16 at the start; afterwards
+// two float32 buffers red[WK][TR][ldr] of K-slice partial tiles, and finally
+// the statistics scratch]
 // [coefficients: 3 KP + 4 NP floats].
+struct P3Adv { int da, db, dpix; };   // positions as rows and columns (mod the image) and pixels
 struct P3Geom {
-    int KP, NP, lda, ldw, ldr, ring;
+    int KP, NP;
     int PW, PH, MP;                 // padded row length W + 2, image height H + 2, positions n PH PW
     int grid, mp_q, mp_r;           // workgroups and MP = mp_q grid + mp_r (set by the launcher)
-    double inv_pw, inv_ph;
-    uint32_t rpw, rph;              // ceil(2^20 / PW), ceil(2^20 / PH): multiply-shift quotients
+    P3Adv ring_adv, epi_adv;        // advance of the ring rows and of the epilogue rows from one batch / tile to the next
     size_t ring_bytes, stage_bytes, lds;
 };
 
 static P3Geom p3_geom(int K, int N, int W)
 {
     P3Geom g;
-    g.KP = (K + 31) / 32 * 32;
+    g.KP = K <= 32 ? 32 : (K <= 64 ? 64 : 128);
     g.NP = N <= 32 ? 32 : (N <= 64 ? 64 : 128);
-    g.lda = g.KP + 8;
-    g.ldw = g.KP + 8;
-    g.ldr = g.NP + 4;
-    g.ring = kP3BM + 2 * (W + 3);
-    g.ring_bytes = (size_t)(g.ring + 17) * g.lda * 2;   // + copies of the first 16 rows + a junk row
+    const int wk = g.KP / 32, wn = g.NP / 32, tr = p3_tile_rows(wk, wn);
+    g.ring_bytes = (size_t)(p3_ring(tr) + p3_copies(wk, wn)) * (g.KP + 8) * 2;
     g.PW = W + 2;
-    g.PH = 0; g.MP = 0; g.inv_pw = 1.0 / g.PW; g.inv_ph = 0.0;   // set by the launcher
+    g.PH = 0; g.MP = 0; g.ring_adv = g.epi_adv = P3Adv{0, 0, 0};   // set by the launcher
     g.grid = 1; g.mp_q = 0; g.mp_r = 0;
-    const size_t wst = (size_t)9 * g.NP * g.ldw * 2;
-    const size_t red = (size_t)(g.KP / 32) * kP3BM * g.ldr * 4;
+    const size_t wst = (size_t)9 * g.KP * g.NP * 2;
+    const size_t red = (size_t)2 * wk * tr * (g.NP + 4) * 4;
     const size_t stats = (size_t)2 * (kP3Threads / (g.NP / 8)) * g.NP * 4;
     g.stage_bytes = wst > red ? wst : red;
     if (stats > g.stage_bytes) g.stage_bytes = stats;
@@ -83,63 +106,53 @@ static P3Geom p3_geom(int K, int N, int W)
     return g;
 }
 
-// Position -> pixel in two steps for the loops: a batch's first position
-// (wave-uniform) is split once, then each lane's offset from it with 24-bit
-// multiply-shift quotients, exact while x d < 2^20 for the dividend x and
-// divisor d (x < PW + 256 against PW <= 64; y < PH + 86 against PH <= kP3MaxH + 2).
-struct P3Base { int img, hp, wp, P; };
-__device__ __forceinline__ P3Base p3_base(int q0, const P3Geom &g)
+// One position of the padded grid, kept as its column and row less one (wq in
+// [-1, W], hq in [-1, H]: both in range means a pixel) with NO byte offsets of
+// its pixel in operands of different pixel strides, and advanced by a tile's
+// rows at a time: adds and selects only (a division or a multiply-shift decode
+// per row and tile was most of the kernel's instructions).  Positions before
+// the first image are padding; those after the last have offsets past the end
+// of every view (raw-buffer loads return zeros), and their outputs are not
+// stored.
+template <int NO> struct P3Walk { int wq, hq; uint32_t off[NO]; };
+template <int NO>
+__device__ __forceinline__ void p3_start(P3Walk<NO> &w, int P, const P3Geom &g, int H, int W, const int *ld)
 {
-    P3Base b;
-    b.P = q0 > 0 ? q0 : 0;
-    const int t = b.P / g.PW;
-    b.wp = b.P - t * g.PW;
-    b.img = t / g.PH;
-    b.hp = t - b.img * g.PH;
-    return b;
+    const int q = P + g.PH * g.PW;                            // P >= -(PW + 1): one image earlier is >= 0
+    const int t = q / g.PW, img = t / g.PH;
+    w.wq = q - t * g.PW - 1;
+    w.hq = t - img * g.PH - 1;
+    const int pix = ((img - 1) * H + w.hq) * W + w.wq;
+    #pragma unroll
+    for (int i = 0; i < NO; i++) w.off[i] += (uint32_t)(pix * ld[i]) * 2u;   // (the caller put its channel there)
 }
-__device__ __forceinline__ int p3_pixel_at(const P3Base &b, int P, const P3Geom &g, int H, int W)
+template <int NO>
+__device__ __forceinline__ void p3_step(P3Walk<NO> &w, const P3Adv &a, const P3Geom &g, int W, const int *ld)
 {
-    const int o = P - b.P;                                    // < 256 (negative only for P < 0)
-    const int x = b.wp + (o > 0 ? o : 0);
-    const int t = (int)(__umul24((uint32_t)x, g.rpw) >> 20);
-    const int wp = x - __mul24(t, g.PW);
-    const int y = b.hp + t;
-    const int u = (int)(__umul24((uint32_t)y, g.rph) >> 20);
-    const int hp = y - __mul24(u, g.PH);
-    const int img = b.img + u;
-    const bool ok = (P >= 0) & (P < g.MP) & (wp > 0) & (wp <= W) & (hp > 0) & (hp <= H);
-    return ok ? (img * H + hp - 1) * W + wp - 1 : -1;
+    w.wq += a.db;
+    const bool cw = w.wq >= g.PW - 1;
+    w.wq -= cw ? g.PW : 0;
+    w.hq += a.da + (cw ? 1 : 0);
+    const bool ch = w.hq >= g.PH - 1;
+    w.hq -= ch ? g.PH : 0;
+    #pragma unroll
+    for (int i = 0; i < NO; i++)
+        w.off[i] += (uint32_t)(a.dpix * ld[i]) * 2u + (cw ? (uint32_t)(-4 * ld[i]) : 0u) +
+                    (ch ? (uint32_t)(-4 * W * ld[i]) : 0u);
 }
-
-// Pixel of padded position P, or -1 for a padding position or one outside
-// [0, MP).  The float64 quotient is within one of the exact one (|P| < 2^30).
-// Branch-free (selects only): the persistent loops keep their loads in
-// flight across it.
-__device__ __forceinline__ int p3_pixel(int P, const P3Geom &g, int H, int W)
+template <int NO> __device__ __forceinline__ bool p3_is_pixel(const P3Walk<NO> &w, int H, int W)
 {
-    int t = (int)((double)P * g.inv_pw);
-    int wp = P - t * g.PW;
-    t = wp < 0 ? t - 1 : (wp >= g.PW ? t + 1 : t);
-    wp = P - t * g.PW;
-    int img = (int)((double)t * g.inv_ph);
-    int hp = t - img * g.PH;
-    img = hp < 0 ? img - 1 : (hp >= g.PH ? img + 1 : img);
-    hp = t - img * g.PH;
-    const bool ok = P >= 0 && P < g.MP && wp > 0 && wp <= W && hp > 0 && hp <= H;
-    return ok ? (img * H + hp - 1) * W + wp - 1 : -1;
+    return ((unsigned)w.wq < (unsigned)W) & ((unsigned)w.hq < (unsigned)H);
 }
 
 // WK x WN: 32-channel K slices x 32-column N slices (one per wave); the
-// other 8 / (WK WN) waves split the tile rows.  The epilogue kind EK and
-// whether the prologue reads a second operand (PRO_BNGRAD) are compile-time,
-// so the epilogue is straight-line code and the compiler can keep the next
-// tile's loads in flight while it waits for the epilogue operand (a runtime
-// mode switch makes it wait for every outstanding load at each branch).
-// PC: the prologue, compile-time where it pays: PC3_BNGRAD (the deferred
-// BN input gradient, which reads a second operand), PC3_BNRELU (the forward
-// BN+ReLU with the statistics epilogue), PC3_RUNTIME (PRO_NONE / PRO_BNRELU /
-// PRO_RELU chosen at run time).
+// other 8 / (WK WN) waves split the tile rows.  The epilogue kind EK and the
+// prologue PC are compile-time, so each part is straight-line code and the
+// compiler's memory counters stay exact across it (a runtime mode switch
+// makes it wait for every outstanding load at each branch).
+// PC: PC3_BNGRAD (the deferred BN input gradient, which reads a second
+// operand), PC3_BNRELU (the forward BN+ReLU with the statistics epilogue),
+// PC3_RUNTIME (PRO_NONE / PRO_BNRELU / PRO_RELU chosen at run time).
 // PC3_BNRELU_SAVE: BN+ReLU whose result z is also stored (the materialised
 // O2' sweep; each workgroup stores the positions of its own range once).
 enum { PC3_RUNTIME = 0, PC3_BNGRAD = 1, PC3_BNRELU = 2, PC3_BNRELU_SAVE = 3 };
@@ -159,28 +172,33 @@ __global__ __launch_bounds__(kP3Threads) void k_conv3x3(RowsParams p, P3Geom g)
     using M = Mfma<T>;
     constexpr int VEC = 8;
     constexpr int KPC = 32 * WK, NPC = 32 * WN;
+    constexpr int TR = p3_tile_rows(WK, WN);                     // rows per tile
     constexpr int WR = 8 / (WK * WN);                            // row groups
-    constexpr int RB = kP3BM / (16 * WR);                        // 16-row blocks per wave
+    constexpr int RB = TR / (16 * WR);                           // 16-row blocks per wave
+    constexpr int VPK = KPC / VEC, SROWS = kP3Threads / VPK;     // vectors per ring row; rows per staging pass
+    constexpr int NVA = (TR + SROWS - 1) / SROWS;                // ring vectors per thread and tile
     constexpr int VPRO = NPC / VEC, RSTEP = kP3Threads / VPRO;
-    constexpr int RPT = kP3BM / RSTEP;                           // epilogue rows per thread
+    constexpr int RPT = (TR + RSTEP - 1) / RSTEP;                // epilogue rows per thread
     constexpr bool READS = EK == EK_STORE_ACC || EK == EK_RELUMASK || BNB;
-    constexpr int NVA = (kP3BM * (KPC / VEC) + kP3Threads - 1) / kP3Threads;
     constexpr int NVB = BNG ? NVA : 1, NVX = READS ? RPT : 1;
-    // batches in flight: one (a second register buffer is merged back into
-    // the first by the compiler, with copies that wait for its loads)
-    constexpr int AHEAD = 1;
-    static_assert(WR * WK * WN == 8 && RPT >= 1, "wave layout");
+    constexpr int FB = p3_fill(TR), RING = p3_ring(TR);          // batches of the first window, ring rows
+    constexpr int COPIES = 16 * RB + 2;
+    static_assert(COPIES == p3_copies(WK, WN) && COPIES <= TR, "ring copies");
+    constexpr int U = 3;                                          // register sets of loads in flight
+    static_assert(WR * WK * WN == 8 && RB >= 1, "wave layout");
     extern __shared__ __align__(16) unsigned char smem[];
-    T *ring = reinterpret_cast<T *>(smem);                       // [ring + 16][lda]
+    T *ring = reinterpret_cast<T *>(smem);                       // [RING + COPIES][lda]
     unsigned char *stage = smem + g.ring_bytes;
-    T *Ws = reinterpret_cast<T *>(stage);                        // [9][NP][ldw] (start only)
-    float *red = reinterpret_cast<float *>(stage);               // [WK][BM][ldr]
+    T *Ws = reinterpret_cast<T *>(stage);                        // [9][KPC][NPC] (start only)
+    float *red = reinterpret_cast<float *>(stage);               // [2][WK][TR][ldr]
     float *coef = reinterpret_cast<float *>(stage + g.stage_bytes);
     float *epi = coef + 3 * KPC;
+    constexpr int lda = KPC + 8, ldr = NPC + 4;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wave % WR, wk = (wave / WR) % WK, wn = wave / (WR * WK);
-    const int K = p.K, N = p.N, RING = g.ring, lda = g.lda, ldr = g.ldr;
+    const int K = p.K, N = p.N;
     const int m = (int)p.m;                                      // launcher: m < 2^30
     const int H = p.h, W = p.w, PW = g.PW;
     // range [floor(b MP / G), floor((b + 1) MP / G)) in 32-bit arithmetic
@@ -189,12 +207,13 @@ __global__ __launch_bounds__(kP3Threads) void k_conv3x3(RowsParams p, P3Geom g)
     const int bid = blockIdx.x;
     const int P0 = bid * g.mp_q + (int)((uint32_t)(bid * g.mp_r) / (uint32_t)g.grid);
     const int P1 = (bid + 1) * g.mp_q + (int)((uint32_t)((bid + 1) * g.mp_r) / (uint32_t)g.grid);
+    const int H1 = PW + 1;
     const T *wsrc = reinterpret_cast<const T *>(p.wraw);
     constexpr uint32_t ES = sizeof(T);
     // operand views as raw buffers (launcher guarantees each spans < 2^31 bytes)
     const int a_ldc = (int)p.a_ldc, a2_ldc = (int)p.a2_ldc, y_ldc = (int)p.y_ldc, ex_ldc = (int)p.ex_ldc;
-    const __amdgpu_buffer_rsrc_t abuf = buf_view(p.a, (uint32_t)(((int64_t)(m - 1) * a_ldc + K) * ES));
-    const __amdgpu_buffer_rsrc_t a2buf = buf_view(BNG ? p.a2 : p.a, BNG ? (uint32_t)(((int64_t)(m - 1) * a2_ldc + K) * ES) : 0u);
+    const uint32_t abytes = (uint32_t)(((int64_t)(m - 1) * a_ldc + K) * ES);
+    const uint32_t a2bytes = BNG ? (uint32_t)(((int64_t)(m - 1) * a2_ldc + K) * ES) : 0u;
     const __amdgpu_buffer_rsrc_t ybuf = buf_view(p.y, (uint32_t)(((int64_t)(m - 1) * y_ldc + N) * ES));
     const int side_ldc = (int)p.side_ldc, ex2_ldc = (int)p.ex2_ldc;
     const __amdgpu_buffer_rsrc_t sbuf = buf_view(SAVE ? p.side : p.a,
@@ -202,36 +221,43 @@ __global__ __launch_bounds__(kP3Threads) void k_conv3x3(RowsParams p, P3Geom g)
     const __amdgpu_buffer_rsrc_t xbuf = buf_view(p.ex ? p.ex : p.y,
                                                  p.ex ? (uint32_t)(((int64_t)(m - 1) * ex_ldc + N) * ES) : 0u);
 
-    // ---- input batches: up to 128 consecutive positions, loaded to registers ----
-    // This thread loads and transforms row tid / 4 of a batch, channel vectors
-    // 4 j + (tid & 3): 4 consecutive lanes cover 64 contiguous bytes of one
-    // pixel, 16 lane groups 16 rows (4 distinct coefficient addresses per
-    // wave: LDS broadcast).  Batch t (positions from P0 + 128 (t + 1) + H1)
-    // replaces ring rows in phase B of tile t; it is loaded AHEAD tiles
-    // earlier into one of two register buffers, so its loads are in flight
-    // for AHEAD tile periods.
-    // own: the position lies in this workgroup's range (SAVE stores it)
-    struct Batch { vec16 a[NVA]; vec16 b[NVB]; int pix; bool own; };
-    auto load_rows = [&](int q0, int cnt, Batch &bt) __attribute__((always_inline)) {
-        const int arow = tid >> 2;
-        const P3Base b = p3_base(q0, g);
-        const int pp = p3_pixel_at(b, q0 + arow, g, H, W);
-        bt.pix = arow < cnt ? pp : -1;
-        bt.own = q0 + arow >= P0 && q0 + arow < P1;
+    // ---- ring rows: this thread's channel vector av of rows ar0, ar0 + SROWS
+    // of each batch of TR consecutive positions (batch b: from P0 - H1 + b TR);
+    // keep: all ones for a pixel, 0 for padding ----
+    constexpr bool STAGES_ALL = SROWS <= TR;                     // else the last waves hold no row of a batch
+    const bool stages = STAGES_ALL || wave * 64 < TR * VPK;
+    const int av = tid % VPK, ar0 = tid / VPK, ac = av * VEC;
+    const bool ac_ok = ac < K && (STAGES_ALL || ar0 < TR);
+    constexpr int NOR = BNG ? 2 : 1;
+    const int rld[2] = {a_ldc, SAVE ? side_ldc : a2_ldc};
+    struct Rows { vec16 a[NVA]; vec16 b[NVB]; uint32_t keep[NVA]; };
+    P3Walk<NOR> rw[NVA];
+    #pragma unroll
+    for (int j = 0; j < NVA; j++) {
+        #pragma unroll
+        for (int i = 0; i < NOR; i++) rw[j].off[i] = (uint32_t)ac * ES;
+        p3_start(rw[j], P0 - H1 + ar0 + j * SROWS, g, H, W, rld);
+    }
+    const int NB = (P1 - P0 + 2 * H1 + TR - 1) / TR;             // batches that an output of this range needs
+    auto load_rows = [&](int b, Rows &bt) __attribute__((always_inline)) {
+        // (a batch past the last needed one reads nothing: an empty view)
+        const __amdgpu_buffer_rsrc_t av_ = buf_view(p.a, b < NB ? abytes : 0u);
+        const __amdgpu_buffer_rsrc_t bv_ = buf_view(BNG ? p.a2 : p.a, b < NB ? a2bytes : 0u);
         #pragma unroll
         for (int j = 0; j < NVA; j++) {
-            const int c = (4 * j + (tid & 3)) * VEC;
-            const bool ok = bt.pix >= 0 && c < K;
-            bt.a[j] = bld16(abuf, ok ? (uint32_t)(bt.pix * a_ldc + c) * ES : kBufOff);
-            if (BNG) bt.b[j < NVB ? j : 0] = bld16(a2buf, ok ? (uint32_t)(bt.pix * a2_ldc + c) * ES : kBufOff);
+            const bool px = p3_is_pixel(rw[j], H, W);
+            bt.keep[j] = px ? 0xffffffffu : 0u;
+            const bool ok = px & ac_ok;
+            bt.a[j] = bld16(av_, ok ? rw[j].off[0] : kBufOff);
+            if (BNG) bt.b[j < NVB ? j : 0] = bld16(bv_, ok ? rw[j].off[NOR - 1] : kBufOff);
+            p3_step(rw[j], g.ring_adv, g, W, rld);
         }
     };
     // ---- prologue loads, in the order they are needed: the per-channel
     // parameters (thread c holds channel c; KPC, NPC <= 128), the weights,
-    // then the ring fill (the first tile's window, positions
-    // [P0 - H1, P0 + 128 + H1) = RING rows in two batches).  Loads complete
-    // in issue order for the wait counter, so the weight staging waits only
-    // for the parameters and the weights, and the fill stays in flight.
+    // then the first tile's window (positions [P0 - H1, P0 + TR + H1)).  Loads
+    // complete in issue order for the wait counter, so the weights wait only
+    // for the parameters, and the window stays in flight.
     //   BNRELU: z = max(x * c0 + c1, 0) with c0 = gamma*rstd, c1 = beta - mean*gamma*rstd
     //   BNGRAD: d = c0 * dy + c1 * x + c2  (the deferred BN input gradient: deferred_coef_of)
     float q0 = 0.f, q1 = 0.f, q2 = 0.f, q3 = 0.f, q4 = 0.f;
@@ -246,59 +272,39 @@ __global__ __launch_bounds__(kP3Threads) void k_conv3x3(RowsParams p, P3Geom g)
     if (tid < N && BNB) { ep0 = p.e_mean[tid]; ep1 = p.e_rstd[tid]; epg = p.e_gamma[tid]; epb = p.e_beta[tid]; }
     if (tid < N && EK == EK_STATS && p.e_shift) ep0 = p.e_shift[tid];     // statistics of y - shift
 
-    // weights -> LDS stage as Ws[tap][n][k] (zero outside K x N), in batches
-    // of kWB vectors per thread whose loads are all in flight before any write
-    constexpr int kWB = 16;
+    // this wave's weight fragments: K slice wk, columns wn*32 + {0, 16}, nine taps
+    typename M::frag bfr[9][2];
     const __amdgpu_buffer_rsrc_t wbuf = buf_view(wsrc, (uint32_t)(9 * K * N * ES));
-    constexpr int wtotal = 9 * KPC * NPC / VEC;
-    constexpr int VPK = KPC / VEC;
-    vec16 wv[kWB];
-    auto load_w = [&](int base) __attribute__((always_inline)) {
+    constexpr int NW = (9 * KPC * VPRO + kP3Threads - 1) / kP3Threads;   // forward: 16-byte vectors per thread
+    vec16 wv[NW];
+    if (!p.wtrans) {      // W[tap][k][n] rows of n (k = c_in, n = c_out), copied as they are
         #pragma unroll
-        for (int u = 0; u < kWB; u++) {
-            if (base + u * kP3Threads >= wtotal) break;      // (uniform: no empty loads issued)
-            const int i = base + u * kP3Threads + tid;
-            int off;
-            if (!p.wtrans) {  // forward: W[tap][k][n] (k = c_in, n = c_out); consecutive lanes take consecutive k
-                const int tap = i / (KPC * VPRO), rem = i % (KPC * VPRO);
-                const int n0 = (rem / KPC) * VEC, k = rem % KPC;
-                off = i < wtotal && k < K && n0 < N ? ((tap * K + k) * N + n0) * (int)ES : (int)kBufOff;
-            } else {          // data gradient: W[8 - tap][n][k] (n = c_in, k = c_out), rows of k
-                const int tap = i / (NPC * VPK), rem = i % (NPC * VPK);
-                const int n = rem / VPK, k0 = (rem % VPK) * VEC;
-                off = i < wtotal && n < N && k0 < K ? (((8 - tap) * N + n) * K + k0) * (int)ES : (int)kBufOff;
-            }
-            wv[u] = bld16(wbuf, (uint32_t)off);
+        for (int u = 0; u < NW; u++) {
+            const int i = tid + u * kP3Threads;
+            const int row = i / VPRO, n0 = (i % VPRO) * VEC, tap = row / KPC, k = row % KPC;
+            const bool ok = tap < 9 && k < K && n0 < N;
+            wv[u] = bld16(wbuf, ok ? (uint32_t)((tap * K + k) * N + n0) * ES : kBufOff);
         }
-    };
-    auto write_w = [&](int base) __attribute__((always_inline)) {
+    } else {              // W[8 - tap][n][k] (n = c_in, k = c_out): rows of k are fragments
         #pragma unroll
-        for (int u = 0; u < kWB; u++) {
-            const int i = base + u * kP3Threads + tid;
-            if (i >= wtotal) break;
-            if (!p.wtrans) {  // scatter the n row to columns (a wave writes 64 consecutive k of a column)
-                const int tap = i / (KPC * VPRO), rem = i % (KPC * VPRO);
-                const int n0 = (rem / KPC) * VEC, k = rem % KPC;
-                #pragma unroll
-                for (int e = 0; e < VEC; e++)
-                    Ws[(tap * NPC + n0 + e) * g.ldw + k] =
-                        (T)((e & 1) ? (wv[u].u[e >> 1] >> 16) : (wv[u].u[e >> 1] & 0xffffu));
-            } else {          // rows copy straight
-                const int tap = i / (NPC * VPK), rem = i % (NPC * VPK);
-                const int n = rem / VPK, k0 = (rem % VPK) * VEC;
-                *reinterpret_cast<vec16 *>(Ws + (tap * NPC + n) * g.ldw + k0) = wv[u];
+        for (int tap = 0; tap < 9; tap++)
+            #pragma unroll
+            for (int cb = 0; cb < 2; cb++) {
+                const int n = wn * 32 + cb * 16 + (lane & 15), k0 = wk * 32 + (lane >> 4) * M::KPL;
+                const bool ok = n < N && k0 < K;
+                const vec16 v = bld16(wbuf, ok ? (uint32_t)(((8 - tap) * N + n) * K + k0) * ES : kBufOff);
+                bfr[tap][cb] = M::from_words(v.u);
             }
+    }
+    Rows fill[FB];
+    #pragma unroll
+    for (int f = 0; f < FB; f++) load_rows(f, fill[f]);
+    if (!p.wtrans) {
+        #pragma unroll
+        for (int u = 0; u < NW; u++) {
+            const int i = tid + u * kP3Threads;
+            if (i < 9 * KPC * VPRO) *reinterpret_cast<vec16 *>(Ws + i * VEC) = wv[u];
         }
-    };
-    load_w(0);
-    const int H1 = g.PW + 1;
-    Batch bt0, bt1;
-    load_rows(P0 - H1, kP3BM, bt0);
-    load_rows(P0 - H1 + kP3BM, RING - kP3BM, bt1);
-    write_w(0);
-    for (int base = kWB * kP3Threads; base < wtotal; base += kWB * kP3Threads) {
-        load_w(base);
-        write_w(base);
     }
     // ---- per-channel prologue / epilogue parameters -> LDS ----
     if (tid < KPC) {
@@ -329,14 +335,15 @@ __global__ __launch_bounds__(kP3Threads) void k_conv3x3(RowsParams p, P3Geom g)
         epi[c] = e0; epi[NPC + c] = e1; epi[2 * NPC + c] = e2; epi[3 * NPC + c] = e3;
     }
     __syncthreads();
-    // this wave's weight fragments: K slice wk, columns wn*32 + {0, 16}, nine taps
-    typename M::frag bfr[9][2];
-    #pragma unroll
-    for (int tap = 0; tap < 9; tap++)
+    if (!p.wtrans) {      // eight consecutive k of one column per lane: transposing reads
+        const int g16 = lane >> 4, j16 = lane & 15;
         #pragma unroll
-        for (int cb = 0; cb < 2; cb++)
-            bfr[tap][cb] = M::load(Ws + (tap * NPC + wn * 32 + cb * 16 + (lane & 15)) * g.ldw + wk * 32 +
-                                   (lane >> 4) * M::KPL);
+        for (int tap = 0; tap < 9; tap++)
+            #pragma unroll
+            for (int cb = 0; cb < 2; cb++)
+                bfr[tap][cb] = tr_frag(Ws + (tap * KPC + wk * 32 + 8 * g16 + (j16 >> 2)) * NPC + wn * 32 + cb * 16 +
+                                           4 * (j16 & 3), NPC);
+    }
     // epilogue channels of this thread are fixed (their BN parameters are
     // read from LDS per tile: registers are the occupancy limit)
     const int v = tid % VPRO, r0 = tid / VPRO;
@@ -351,275 +358,312 @@ __global__ __launch_bounds__(kP3Threads) void k_conv3x3(RowsParams p, P3Geom g)
         #pragma unroll
         for (int e = 0; e < VEC; e++) zs = zs && ga[e] != 0.f;
     }
-    const T *zsrc_col = reinterpret_cast<const T *>(zs ? p.ex : (p.ex2 ? p.ex2 : p.ex)) + (col_ok ? n : 0);
+    const char *zsrc_base = reinterpret_cast<const char *>(zs ? p.ex : (p.ex2 ? p.ex2 : p.ex));
     const int zsrc_ldc = zs ? ex_ldc : ex2_ldc;
 
-    // ---- prologue transform of a batch, then the ring writes.  The mode
-    // switch is wave-uniform and outside the vector loop; invalid rows are
-    // zeroed on the packed words and rows past the batch go to a junk row, so
-    // each mode's vectors are straight-line code; only the copies of the first
-    // 16 ring rows are written under a branch (around stores, no loads).
-    // 32 NVA = KPC: every channel vector is in range. ----
-    static_assert(32 * NVA == KPC, "batch vectors");
-    auto store_rows = [&](int cnt, int slot0, Batch &bt) __attribute__((always_inline)) {
-        const int arow = tid >> 2;
-        const vec16 *ra = bt.a, *rb = bt.b;
-        int s = slot0 + arow;
-        s = s >= RING ? s - RING : s;
-        const bool live = arow < cnt;
-        const int s1 = live ? s : RING + 16;
-        const int s2 = live && s < 16 ? s + RING : RING + 16;
-        const uint32_t keep = bt.pix >= 0 ? 0xffffffffu : 0u;    // padding rows: zeros
+    // ---- prologue transform of batch b, then the ring writes (slot0: its ring
+    // slot, a multiple of TR).  The mode switch is wave-uniform and outside the
+    // vector loop; padding rows are zeroed by the ReLU's upper clamp (BNRELU)
+    // or on the packed words; only the copies of the first ring rows are
+    // written under a branch (around stores, no loads). ----
+    float kc0[VEC], kc1[VEC];                        // BNRELU: this thread's channels' coefficients
+    if (pro == PRO_BNRELU) { lds_f8(coef + ac, kc0); lds_f8(coef + KPC + ac, kc1); }
+    else
+        #pragma unroll
+        for (int e = 0; e < VEC; e++) { kc0[e] = 0.f; kc1[e] = 0.f; }
+    T *ring_w = ring + ar0 * lda + ac;
+    P3Walk<1> sw[SAVE ? NVA : 1];                    // SAVE: the staged rows (behind the loads by FB + U batches)
+    if (SAVE)
+        #pragma unroll
+        for (int j = 0; j < NVA; j++) {
+            sw[j].off[0] = (uint32_t)ac * ES;
+            p3_start(sw[j], P0 - H1 + ar0 + j * SROWS, g, H, W, rld + 1);
+        }
+    auto store_rows = [&](int b, int slot0, Rows &bt) __attribute__((always_inline)) {
         vec16 outv[NVA];
         if (BNG) {                                        // PRO_BNGRAD: d = c0 dy + c1 x + c2
+            float c0[VEC], c1[VEC], c2[VEC];
+            lds_f8(coef + ac, c0);
+            lds_f8(coef + KPC + ac, c1);
+            lds_f8(coef + 2 * KPC + ac, c2);
             #pragma unroll
             for (int j = 0; j < NVA; j++) {
-                const int c = (4 * j + (tid & 3)) * VEC;
-                float f[VEC], x[VEC], c0[VEC], c1[VEC], c2[VEC];
-                Elem<T>::unpack(ra[j], f);
-                Elem<T>::unpack(rb[j < NVB ? j : 0], x);
-                lds_f8(coef + c, c0);
-                lds_f8(coef + KPC + c, c1);
-                lds_f8(coef + 2 * KPC + c, c2);
+                float f[VEC], x[VEC];
+                Elem<T>::unpack(bt.a[j], f);
+                Elem<T>::unpack(bt.b[j < NVB ? j : 0], x);
                 #pragma unroll
                 for (int e = 0; e < VEC; e++) f[e] = __builtin_fmaf(c0[e], f[e], __builtin_fmaf(c1[e], x[e], c2[e]));
                 outv[j] = Elem<T>::pack(f);
                 #pragma unroll
-                for (int i = 0; i < 4; i++) outv[j].u[i] &= keep;
+                for (int i = 0; i < 4; i++) outv[j].u[i] &= bt.keep[j];
             }
-        } else if (pro == PRO_BNRELU) {                   // z = max(x c0 + c1, 0)
+        } else if (pro == PRO_BNRELU) {                   // z = max(x c0 + c1, 0); padding: clamped to [0, 0]
             #pragma unroll
             for (int j = 0; j < NVA; j++) {
-                const int c = (4 * j + (tid & 3)) * VEC;
-                float f[VEC], ca[VEC], cb[VEC];
-                Elem<T>::unpack(ra[j], f);
-                lds_f8(coef + c, ca);
-                lds_f8(coef + KPC + c, cb);
+                float f[VEC];
+                Elem<T>::unpack(bt.a[j], f);
+                const float top = __uint_as_float(bt.keep[j] & 0x7f800000u);     // +inf or 0
                 #pragma unroll
-                for (int e = 0; e < VEC; e++) f[e] = __builtin_fmaxf(bn_lin(f[e], ca[e], cb[e]), 0.f);
+                for (int e = 0; e < VEC; e++) f[e] = __builtin_amdgcn_fmed3f(bn_lin(f[e], kc0[e], kc1[e]), 0.f, top);
                 outv[j] = Elem<T>::pack(f);
-                #pragma unroll
-                for (int i = 0; i < 4; i++) outv[j].u[i] &= keep;
-                if (SAVE)
-                    bst16(sbuf, live && bt.own && bt.pix >= 0 && c < K ? (uint32_t)(bt.pix * side_ldc + c) * ES : kBufOff,
-                          outv[j]);
             }
         } else if (pro == PRO_RELU) {                     // (padding rows load zeros)
             #pragma unroll
             for (int j = 0; j < NVA; j++) {
                 float f[VEC];
-                Elem<T>::unpack(ra[j], f);
+                Elem<T>::unpack(bt.a[j], f);
                 #pragma unroll
                 for (int e = 0; e < VEC; e++) f[e] = __builtin_fmaxf(f[e], 0.f);
                 outv[j] = Elem<T>::pack(f);
             }
         } else {
             #pragma unroll
-            for (int j = 0; j < NVA; j++) outv[j] = ra[j];     // out-of-range loads read zero
+            for (int j = 0; j < NVA; j++) outv[j] = bt.a[j];     // padding rows load zeros
         }
+        T *dst = ring_w + slot0 * lda;
         #pragma unroll
-        for (int j = 0; j < NVA; j++) {
-            const int c = (4 * j + (tid & 3)) * VEC;
-            *reinterpret_cast<vec16 *>(ring + s1 * lda + c) = outv[j];
-        }
-        // the copies of the first 16 ring rows: a branch around stores only
-        // (most waves hold none of those rows and skip the writes)
-        if (s2 != RING + 16)
+        for (int j = 0; j < NVA; j++) *reinterpret_cast<vec16 *>(dst + j * SROWS * lda) = outv[j];
+        if (slot0 == 0)
+            #pragma unroll
+            for (int j = 0; j < NVA; j++)
+                if (j * SROWS < COPIES && ar0 + j * SROWS < COPIES)
+                    *reinterpret_cast<vec16 *>(dst + (RING + j * SROWS) * lda) = outv[j];
+        if (SAVE)
             #pragma unroll
             for (int j = 0; j < NVA; j++) {
-                const int c = (4 * j + (tid & 3)) * VEC;
-                *reinterpret_cast<vec16 *>(ring + s2 * lda + c) = outv[j];
+                const int q = b * TR - H1 + ar0 + j * SROWS;     // stored by the workgroup that owns the position
+                const bool ok = (q >= 0) & (q < P1 - P0) & (bt.keep[j] != 0u) & ac_ok;
+                bst16(sbuf, ok ? sw[j].off[0] : kBufOff, outv[j]);
+                p3_step(sw[j], g.ring_adv, g, W, rld + 1);
             }
     };
 
     // ---- epilogue operand: thread = one channel vector of rows r0, r0+RSTEP, ... ----
-    vec16 rx[NVX];
-    int epix[RPT];                  // pixels of this thread's epilogue rows (-1: padding / past the end)
+    struct Epi { vec16 x[NVX]; uint32_t yoff[RPT]; };   // yoff: kBufOff for padding / past the end
+    // ALT: a tile's rows are half of the threads' vectors; the waves of the
+    // first half take the even tiles, the others the odd ones (thread r0 holds
+    // row r0 of a pair of tiles)
+    constexpr bool ALT = RSTEP > TR;
+    static_assert(!ALT || (RSTEP == 2 * TR && RPT == 1), "epilogue rows");
+    const int half = ALT ? wave * 64 / (TR * VPRO) : 0;
+    auto epi_mine = [&](int tile) __attribute__((always_inline)) -> bool { return !ALT || (tile & 1) == half; };
+    constexpr bool XOP = EK == EK_RELUMASK || BNB;   // an operand of its own
+    constexpr int NOE = XOP ? 2 : 1;
+    const int eld[2] = {y_ldc, ZK ? zsrc_ldc : ex_ldc};
+    P3Walk<NOE> ew[RPT];
     float s1[VEC], s2[VEC];
     #pragma unroll
     for (int e = 0; e < VEC; e++) { s1[e] = 0.f; s2[e] = 0.f; }
-    auto load_epi = [&](int p0, int nrows) __attribute__((always_inline)) {
-        const P3Base eb = p3_base(p0, g);
+    #pragma unroll
+    for (int j = 0; j < RPT; j++) {
+        #pragma unroll
+        for (int i = 0; i < NOE; i++) ew[j].off[i] = (uint32_t)n * ES;
+        p3_start(ew[j], P0 + r0 + j * RSTEP, g, H, W, eld);
+    }
+    auto load_epi = [&](int t, Epi &ep) __attribute__((always_inline)) {
+        const int nrows = P1 - P0 - t * TR;                      // (may be past the end: no row)
         #pragma unroll
         for (int j = 0; j < RPT; j++) {
-            const int r = r0 + j * RSTEP;
-            const int pp = p3_pixel_at(eb, p0 + r, g, H, W);
-            epix[j] = col_ok && r < nrows ? pp : -1;
-        }
-        if (!READS) return;
-        #pragma unroll
-        for (int j = 0; j < NVX; j++) {
-            const int pp = epix[j];
-            const bool ok = pp >= 0;
-            if (EK == EK_STORE_ACC) {
-                rx[j] = bld16(ybuf, ok ? (uint32_t)(pp * y_ldc + n) * ES : kBufOff);
-            } else if (ZK) {   // z, or x (gamma = 0 in the vector): one load from this thread's
+            const int r = (ALT ? r0 % TR : r0) + j * RSTEP;
+            const bool ok = p3_is_pixel(ew[j], H, W) & col_ok & (r < nrows);
+            ep.yoff[j] = ok ? ew[j].off[0] : kBufOff;
+            if (EK == EK_STORE_ACC) ep.x[j < NVX ? j : 0] = bld16(ybuf, ep.yoff[j]);
+            else if (ZK)       // z, or x (gamma = 0 in the vector): one load from this thread's
                 // source at a clamped pixel (a padding or past-the-end row is not used)
-                rx[j] = ldg16(zsrc_col + (int64_t)(ok ? pp : 0) * zsrc_ldc);
-            } else {
-                rx[j] = bld16(xbuf, ok ? (uint32_t)(pp * ex_ldc + n) * ES : kBufOff);
-            }
+                ep.x[j < NVX ? j : 0] = ldg16(zsrc_base + (ok ? ew[j].off[NOE - 1] : 0u));
+            else if (XOP) ep.x[j < NVX ? j : 0] = bld16(xbuf, ok ? ew[j].off[NOE - 1] : kBufOff);
+            p3_step(ew[j], g.epi_adv, g, W, eld);
         }
     };
 
-    // ---- ring fill (slots 0 .. RING-1), then the first AHEAD batches and
-    // the first tile's epilogue operand (issued first: a wait for it then
-    // leaves the batches in flight) ----
-    store_rows(kP3BM, 0, bt0);
-    store_rows(RING - kP3BM, kP3BM, bt1);
-    auto batch_rows = [&](int t) __attribute__((always_inline)) -> int {
-        const int c = P1 + H1 - (P0 + kP3BM + H1 + t * kP3BM);
-        return c < 0 ? 0 : (c > kP3BM ? kP3BM : c);
-    };
-    load_epi(P0, P1 - P0 < kP3BM ? P1 - P0 : kP3BM);
-    if (batch_rows(0) > 0) load_rows(P0 + kP3BM + H1, batch_rows(0), bt0);
-    if (AHEAD == 2 && batch_rows(1) > 0) load_rows(P0 + 2 * kP3BM + H1, batch_rows(1), bt1);
-    int sb = H1;                    // ring slot of the first row of the current tile
+    // ---- the first window, then the loads of the first iterations ----
+    if (stages)
+        #pragma unroll
+        for (int f = 0; f < FB; f++) store_rows(f, f * TR, fill[f]);
+    const int NT = (P1 - P0 + TR - 1) / TR;
+    // set i holds, for the iterations t = i mod U, ring batch FB + t and the
+    // epilogue operand of tile t - 1
+    Rows rs[U];
+    Epi es[U];
+    #pragma unroll
+    for (int i = 0; i < U; i++) {
+        load_rows(FB + i, rs[i]);
+        if (i > 0 && epi_mine(i - 1)) load_epi(i - 1, es[i]);
+    }
+    #pragma unroll
+    for (int j = 0; j < RPT; j++) es[0].yoff[j] = kBufOff;       // (no tile before the first)
+    #pragma unroll
+    for (int j = 0; j < NVX; j++) es[0].x[j] = zero16();
     __syncthreads();
 
-    // Per tile two phases separated by barriers: (A) matrix cores on the
-    // tile's ring window, partial tiles to LDS; (B) the ring rows of the tile
-    // after next's window replace the rows only this tile needed, the
-    // epilogue of this tile runs, and the next batch and epilogue operand are
-    // loaded.
-    auto tile = [&](int p0, Batch &bt) __attribute__((always_inline)) {
-        const int tt = (p0 - P0) / kP3BM;
+    const int lane_off = (lane & 15) * lda + wk * 32 + (lane >> 4) * M::KPL;
+    int sb = wr * 16 * RB;          // ring slot of tile row (wr 16 RB) less H1
+    int ss = FB * TR;               // ring slot of the batch being written
 
-        // ---- (A) matrix cores: 16 RB rows x 32 columns x 32 K per wave, nine taps ----
+    // ---- matrix cores on tile t: 16 RB rows x 32 columns x 32 K per wave, nine taps ----
+    auto mma_tile = [&](int t) __attribute__((always_inline)) {
         f32x4 acc[RB][2];               // set by the first tap's products
-        // A fragment = ring row u (wave-uniform) + this lane's fixed offset;
-        // the next tap's fragments are read while this tap's are multiplied
-        const int lane_off = (lane & 15) * lda + wk * 32 + (lane >> 4) * M::KPL;
-        const int ubase = sb + __builtin_amdgcn_readfirstlane(wr) * 16 * RB;
-        // (double-buffered unless the 128-column variants' registers cannot hold it)
-        constexpr int NB = WN == 4 ? 1 : 2;
-        typename M::frag af[NB][RB];
+        // one address per filter row (the ring rows from tap column -1 on; the
+        // copies make them contiguous): the taps and 16-row blocks of a filter
+        // row are immediate offsets.  The next tap's fragments are read while
+        // this tap's are multiplied
+        const T *abase[3];
+        #pragma unroll
+        for (int kh = 0; kh < 3; kh++) {
+            int u = sb + kh * PW;                        // (H1 - 1 = PW)
+            u = u >= RING ? u - RING : u;
+            abase[kh] = ring + u * lda + lane_off;
+        }
+        typename M::frag af[2][RB];
         auto load_tap = [&](int tap, typename M::frag *dst) __attribute__((always_inline)) {
-            const int off = (tap / 3 - 1) * PW + (tap % 3 - 1);
             #pragma unroll
-            for (int ib = 0; ib < RB; ib++) {
-                int u = ubase + ib * 16 + off;           // in [-(PW + 1), 2 RING)
-                u = u < 0 ? u + RING : (u >= RING ? u - RING : u);
-                dst[ib] = M::load(ring + u * lda + lane_off);
-            }
+            for (int ib = 0; ib < RB; ib++) dst[ib] = M::load(abase[tap / 3] + (tap % 3 + ib * 16) * lda);
         };
-        if (NB == 2) load_tap(0, af[0]);
+        load_tap(0, af[0]);
         #pragma unroll
         for (int tap = 0; tap < 9; tap++) {
-            if (NB == 1) load_tap(tap, af[0]);
-            else if (tap + 1 < 9) load_tap(tap + 1, af[(tap + 1) % NB]);
+            if (tap + 1 < 9) load_tap(tap + 1, af[(tap + 1) % 2]);
+            __builtin_amdgcn_sched_barrier(0);
             #pragma unroll
             for (int ib = 0; ib < RB; ib++) {
                 if (tap == 0) {
                     M::mma0(acc[ib][0], bfr[0][0], af[0][ib]);
                     M::mma0(acc[ib][1], bfr[0][1], af[0][ib]);
                 } else {
-                    M::mma(acc[ib][0], bfr[tap][0], af[tap % NB][ib]);
-                    M::mma(acc[ib][1], bfr[tap][1], af[tap % NB][ib]);
+                    M::mma(acc[ib][0], bfr[tap][0], af[tap % 2][ib]);
+                    M::mma(acc[ib][1], bfr[tap][1], af[tap % 2][ib]);
                 }
             }
         }
-        // ---- float32 partial tile of this K slice -> LDS (the weights are
-        // the matrix cores' first operand, so a lane holds four consecutive
-        // channels of one position: one 16-byte write) ----
+        // float32 partial tile of this K slice -> LDS (the weights are the
+        // matrix cores' first operand, so a lane holds four consecutive
+        // channels of one position: one 16-byte write)
+        float *rd = red + (t & 1) * (WK * TR * ldr);
         #pragma unroll
         for (int ib = 0; ib < RB; ib++)
             #pragma unroll
             for (int cb = 0; cb < 2; cb++) {
                 const int row = wr * 16 * RB + ib * 16 + (lane & 15);
                 const int col = wn * 32 + cb * 16 + (lane >> 4) * 4;
-                *reinterpret_cast<f32x4 *>(red + (wk * kP3BM + row) * ldr + col) = acc[ib][cb];
+                *reinterpret_cast<f32x4 *>(rd + (wk * TR + row) * ldr + col) = acc[ib][cb];
             }
-        __syncthreads();
-        // ---- (B) ring rows of the tile after next, then this tile's epilogue ----
-        store_rows(batch_rows(tt), (tt * kP3BM) % RING, bt);
-        // ---- epilogue row pass: sum of the K slices (fixed order), rounded to
-        // the storage type; all outputs of this thread first (no branch,
-        // invalid rows contribute zeros), then the stores back to back ----
-        {
-            vec16 vo[RPT];
-            float eM[VEC], eR[VEC], eC0[VEC], eC1[VEC];
-            if (EK == EK_STATS) lds_f8(epi + n, eM);                  // shift
-            if (BNB) {
-                lds_f8(epi + n, eM);
-                lds_f8(epi + NPC + n, eR);
-                lds_f8(epi + 2 * NPC + n, eC0);
-                lds_f8(epi + 3 * NPC + n, eC1);
-            }
+    };
+    // ---- epilogue of tile t - 1: sum of the K slices (fixed order), rounded
+    // to the storage type; all outputs of this thread first (no branch, invalid
+    // rows contribute zeros), then the stores back to back ----
+    auto epi_tile = [&](int t, Epi &ep) __attribute__((always_inline)) {
+        const float *rd = red + ((t - 1) & 1) * (WK * TR * ldr) + (ALT ? r0 % TR : r0) * ldr + n;
+        vec16 vo[RPT];
+        float eM[VEC], eC0[VEC], eC1[VEC];
+        if (BNB) {
+            lds_f8(epi + n, eM);
+            lds_f8(epi + 2 * NPC + n, eC0);
+            lds_f8(epi + 3 * NPC + n, eC1);
+        }
+        #pragma unroll
+        for (int j = 0; j < RPT; j++) {
+            const bool ok = (int)ep.yoff[j] >= 0;
+            float f[VEC];
             #pragma unroll
-            for (int j = 0; j < RPT; j++) {
-                const int r = r0 + j * RSTEP;
-                const bool ok = epix[j] >= 0;
-                float f[VEC];
-                #pragma unroll
-                for (int e = 0; e < VEC; e++) f[e] = 0.f;
-                #pragma unroll
-                for (int q = 0; q < WK; q++) {
-                    const float4 *src = reinterpret_cast<const float4 *>(red + (q * kP3BM + r) * ldr + n);
-                    const float4 lo = src[0], hi = src[1];
+            for (int q = 0; q < WK; q++) {
+                const float4 *src = reinterpret_cast<const float4 *>(rd + (q * TR + j * RSTEP) * ldr);
+                const float4 lo = src[0], hi = src[1];
+                if (q == 0) {
+                    f[0] = lo.x; f[1] = lo.y; f[2] = lo.z; f[3] = lo.w;
+                    f[4] = hi.x; f[5] = hi.y; f[6] = hi.z; f[7] = hi.w;
+                } else {
                     f[0] += lo.x; f[1] += lo.y; f[2] += lo.z; f[3] += lo.w;
                     f[4] += hi.x; f[5] += hi.y; f[6] += hi.z; f[7] += hi.w;
                 }
-                const vec16 cv = Elem<T>::pack(f);
-                Elem<T>::unpack(cv, f);
-                vo[j] = cv;
-                if (EK == EK_STORE_ACC) {
-                    float old[VEC];
-                    Elem<T>::unpack(rx[j < NVX ? j : 0], old);
-                    #pragma unroll
-                    for (int e = 0; e < VEC; e++) f[e] += old[e];
-                    vo[j] = Elem<T>::pack(f);
-                } else if (EK == EK_STATS) {
-                    #pragma unroll
-                    for (int e = 0; e < VEC; e++) {
-                        const float fv = ok ? f[e] - eM[e] : 0.f;
-                        s1[e] += fv;
-                        s2[e] += fv * fv;
-                    }
-                } else if (EK == EK_RELUMASK) {
-                    float yv[VEC];
-                    Elem<T>::unpack(rx[j < NVX ? j : 0], yv);
-                    #pragma unroll
-                    for (int e = 0; e < VEC; e++) f[e] = yv[e] > 0.f ? f[e] : 0.f;
-                    vo[j] = Elem<T>::pack(f);
-                } else if (BNB) {
-                    float x[VEC];
-                    Elem<T>::unpack(rx[j < NVX ? j : 0], x);
-                    #pragma unroll
-                    for (int e = 0; e < VEC; e++) {
-                        const float xh = (x[e] - eM[e]) * eR[e];
-                        const float d = ok && bn_lin(x[e], eC0[e], eC1[e]) > 0.f ? f[e] : 0.f;
-                        f[e] = d;
-                        s1[e] += d;
-                        s2[e] += d * xh;
-                    }
-                    vo[j] = Elem<T>::pack(f);
-                }
             }
-            #pragma unroll
-            for (int j = 0; j < RPT; j++)
-                bst16(ybuf, epix[j] >= 0 ? (uint32_t)(epix[j] * y_ldc + n) * ES : kBufOff, vo[j]);
+            const vec16 cv = Elem<T>::pack(f);
+            vo[j] = cv;
+            if (EK == EK_STORE_ACC) {
+                float old[VEC];
+                Elem<T>::unpack(cv, f);
+                Elem<T>::unpack(ep.x[j < NVX ? j : 0], old);
+                #pragma unroll
+                for (int e = 0; e < VEC; e++) f[e] += old[e];
+                vo[j] = Elem<T>::pack(f);
+            } else if (EK == EK_STATS) {      // (rows that are not stored count as zeros)
+                vec16 cm = cv;
+                const uint32_t keep = ok ? 0xffffffffu : 0u;
+                #pragma unroll
+                for (int i = 0; i < 4; i++) cm.u[i] &= keep;
+                Elem<T>::unpack(cm, f);
+                if (p.e_shift) {
+                    lds_f8(epi + n, eM);
+                    #pragma unroll
+                    for (int e = 0; e < VEC; e++) f[e] -= ok ? eM[e] : 0.f;
+                }
+                #pragma unroll
+                for (int e = 0; e < VEC; e++) {
+                    s1[e] += f[e];
+                    s2[e] = __builtin_fmaf(f[e], f[e], s2[e]);
+                }
+            } else if (EK == EK_RELUMASK) {
+                float yv[VEC];
+                Elem<T>::unpack(cv, f);
+                Elem<T>::unpack(ep.x[j < NVX ? j : 0], yv);
+                #pragma unroll
+                for (int e = 0; e < VEC; e++) f[e] = yv[e] > 0.f ? f[e] : 0.f;
+                vo[j] = Elem<T>::pack(f);
+            } else if (BNB) {                 // (xhat's rstd multiplies the finished sum)
+                float x[VEC];
+                vec16 cm = cv;
+                const uint32_t keep = ok ? 0xffffffffu : 0u;
+                #pragma unroll
+                for (int i = 0; i < 4; i++) cm.u[i] &= keep;
+                Elem<T>::unpack(cm, f);
+                Elem<T>::unpack(ep.x[j < NVX ? j : 0], x);
+                #pragma unroll
+                for (int e = 0; e < VEC; e++) {
+                    const float d = bn_lin(x[e], eC0[e], eC1[e]) > 0.f ? f[e] : 0.f;
+                    f[e] = d;
+                    s1[e] += d;
+                    s2[e] = __builtin_fmaf(d, x[e] - eM[e], s2[e]);
+                }
+                vo[j] = Elem<T>::pack(f);
+            }
         }
-        // unconditional (past the end: zero rows, out-of-range offsets), so the
-        // compiler's memory counters stay exact across the loop
-        load_epi(p0 + kP3BM, P1 - p0 - kP3BM < kP3BM ? (P1 - p0 - kP3BM > 0 ? P1 - p0 - kP3BM : 0) : kP3BM);
-        load_rows(P0 + kP3BM + H1 + (tt + AHEAD) * kP3BM, batch_rows(tt + AHEAD), bt);
-        sb += kP3BM;
+        #pragma unroll
+        for (int j = 0; j < RPT; j++) bst16(ybuf, ep.yoff[j], vo[j]);
+    };
+
+    // iteration t (0 .. NT): tile t on the matrix cores, epilogue of tile
+    // t - 1, ring rows of tile t + 1; then the set's loads for iteration t + U
+    // (unconditional: past the end they read nothing)
+    const bool mma_first = wave < 4;
+    auto iter = [&](int t, Rows &bt, Epi &ep) __attribute__((always_inline)) {
+        if (mma_first && t < NT) mma_tile(t);
+        if (epi_mine(t - 1)) epi_tile(t, ep);
+        if (stages) store_rows(FB + t, ss, bt);
+        load_rows(FB + t + U, bt);
+        if (epi_mine(t + U - 1)) load_epi(t + U - 1, ep);
+        if (!mma_first && t < NT) mma_tile(t);
+        sb += TR;
         if (sb >= RING) sb -= RING;
+        ss += TR;
+        if (ss >= RING) ss -= RING;
         __syncthreads();
     };
-    for (int p0 = P0; p0 < P1; p0 += 2 * kP3BM) {
-        tile(p0, bt0);
-        if (p0 + kP3BM >= P1) break;
-        tile(p0 + kP3BM, AHEAD == 2 ? bt1 : bt0);
+    for (int t = 0; t <= NT; t += U) {
+        iter(t, rs[0], es[0]);
+        if (t + 1 > NT) break;
+        iter(t + 1, rs[1], es[1]);
+        if (t + 2 > NT) break;
+        iter(t + 2, rs[2], es[2]);
     }
+    static_assert(U == 3, "unrolled by the register sets");
 
     // ---- per-workgroup statistics partial row ----
     if (EK == EK_STATS || BNB) {
+        float eR[VEC];
+        if (BNB) lds_f8(epi + NPC + n, eR);
         #pragma unroll
         for (int e = 0; e < VEC; e++) {
             red[r0 * NPC + n + e] = s1[e];
-            red[(RSTEP + r0) * NPC + n + e] = s2[e];
+            red[(RSTEP + r0) * NPC + n + e] = BNB ? s2[e] * eR[e] : s2[e];
         }
         lds_colsum2(red, RSTEP, NPC, NPC, kP3Threads, tid, p.part + (int64_t)blockIdx.x * 2 * N,
                     p.part + (int64_t)blockIdx.x * 2 * N + N, N);
@@ -644,7 +688,7 @@ bool conv3x3_supported(int dtype, int K, int N, int H, int W)
     if (dtype != DT_BF16 || K > 128 || N > 128 || W > kP3MaxW || W < 1 || H > kP3MaxH || H < 1) return false;
     const P3Geom g = p3_geom(K, N, W);
     const int wk = g.KP / 32, wn = g.NP / 32;
-    if (wk == 3 || wk * wn > 4) return false;      // at most 64 rows x 2 column blocks of accumulators per wave
+    if (wk * wn > 4) return false;                 // every wave one K and one N slice, at least two row groups
     return g.lds <= 160 * 1024;
 }
 
@@ -738,9 +782,17 @@ hipError_t launch_conv3x3(const RowsParams &p, hipStream_t s)
         return hipErrorInvalidValue;
     P3Geom g = p3_geom(p.K, p.N, p.w);
     g.PH = p.h + 2;
-    g.inv_ph = 1.0 / g.PH;
-    g.rpw = (uint32_t)(((1u << 20) + g.PW - 1) / g.PW);
-    g.rph = (uint32_t)(((1u << 20) + g.PH - 1) / g.PH);
+    const auto advance = [&](int positions) {
+        const int rows = positions / g.PW;
+        P3Adv a;
+        a.db = positions % g.PW;
+        a.da = rows % g.PH;
+        a.dpix = rows / g.PH * (p.h * p.w) + a.da * p.w + a.db;
+        return a;
+    };
+    const int tr = p3_tile_rows(g.KP / 32, g.NP / 32);
+    g.ring_adv = advance(tr);
+    g.epi_adv = advance(kP3Threads / (g.NP / 8) > tr ? 2 * tr : tr);      // (k_conv3x3: ALT)
     const int64_t mp = (int64_t)p.n * g.PH * g.PW;                // padded positions
     if (mp >= (lim >> 1)) return hipErrorInvalidValue;
     g.MP = (int)mp;

@@ -1,0 +1,120 @@
+"""Edges of the kernels' tiles and dispatch rules, against the CPU oracle (GPU).
+
+Each case runs one BN-ReLU-CONV layer forward (with the statistics of its
+output) and backward (dense gradient, and the deferred gradient of the BN
+after it) at a size where a tile, a remainder or a rule of the dispatch turns,
+and compares every output with the fp64 oracle on the same inputs.  Tolerances
+are those of the parity tests (helpers.RTOL: max |gpu - ref| / max |ref|); the
+per-channel sums are bounded by the sum of their terms' magnitudes, and
+elements whose ReLU decision lies within rounding of 0 are excluded.
+"""
+import numpy as np
+import pytest
+import torch
+
+from helpers import RTOL, assert_close, assert_stats, bf16_round, dev, f32dev, host, relu_ambiguous
+from oracle import prims as P
+from paper_1807_01702_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_1807_01702_amd import bnr
+    return bnr
+
+
+def _layer(B, bf16, k, n, h, w, ci, co, seed=11, pad_in=0, pad_out=0):
+    """Runs the layer both ways on views of wider buffers; returns nothing, asserts."""
+    rnd = bf16_round if bf16 else (lambda a: np.asarray(a, np.float64))
+    rtol, m = RTOL[bf16], n * h * w
+    xf = synth.normal(seed, "x", (n, h, w, ci + pad_in), bf16=bf16)
+    wt = synth.conv_weight(seed, "w", k, ci, co, bf16)
+    p1, p2 = synth.bn_params(seed, "bn1", ci), synth.bn_params(seed, "bn2", co)
+    x64 = xf[..., :ci].astype(np.float64)
+    y1, mu, var, rstd = P.bn_fwd(x64.reshape(m, ci), p1["gamma"], p1["beta"], 1e-5)
+    z = rnd(P.relu_fwd(y1).reshape(n, h, w, ci))
+    out_r = rnd(P.conv_fwd(z, wt.astype(np.float64)))
+    x = dev(xf, bf16)[..., :ci]
+    wd = dev(wt, bf16)
+    buf = torch.full((n, h, w, co + pad_out), 7.0, dtype=x.dtype, device=x.device)
+    out = buf[..., :co]
+    bn1 = B.BN(f32dev(p1["gamma"]), f32dev(p1["beta"]), 1e-5, f32dev(mu), f32dev(var), f32dev(rstd))
+    bn2 = B.BN(f32dev(p2["gamma"]), f32dev(p2["beta"]), 1e-5)
+    desc = B.desc_for(x, out, k, n, h, w)
+    B.workspace(B.bnr_workspace_size(desc), x.device)
+    B._ws_cache[(x.device, 0)].fill_(255)                   # NaN: nothing may read what the call did not write
+    B.bnr_bn_relu_conv_fwd(desc, x, bn1, wd, out, bn2)
+    torch.cuda.synchronize()
+    assert_close("out", host(out), out_r, rtol)
+    assert bool((buf[..., co:] == 7.0).all()), "the forward wrote past its channels"
+    o64 = host(out).reshape(m, co)
+    mo, vo, ro = P.bn_stats(o64, 1e-5)
+    if m > 1:
+        assert_stats("out", host(bn2.mean), host(bn2.var), mo, vo, 1e-4)
+
+    # backward: dense gradient, then the deferred gradient of a BN reading out
+    gf = synth.normal(seed, "g", (n, h, w, co), bf16=bf16)
+    gd = dev(gf, bf16)
+    dgn, dbn = f32dev(synth.normal(seed, "dgn", (co,))), f32dev(synth.normal(seed, "dbn", (co,)))
+    bn2.mean.copy_(f32dev(mo)), bn2.rstd.copy_(f32dev(np.minimum(ro, 10.0)))
+    mo32, ro32 = host(bn2.mean), host(bn2.rstd)
+    xh_o = (o64 - mo32) * ro32
+    k2 = p2["gamma"] * ro32
+    g2 = rnd((k2 * (gf.reshape(m, co) - host(dbn) / m - xh_o * host(dgn) / m)).reshape(n, h, w, co))
+    for name, src, g in (("dense", B.grad_dense(gd), gf.astype(np.float64)),
+                         ("deferred", B.grad_bn(gd, out, bn2, dgn, dbn), g2)):
+        dw = torch.empty(tuple(wt.shape), dtype=torch.float32, device=x.device)
+        dga, dbe = (torch.empty(ci, dtype=torch.float32, device=x.device) for _ in range(2))
+        dy = torch.empty((n, h, w, ci), dtype=x.dtype, device=x.device)
+        B._ws_cache[(x.device, 0)].fill_(255)
+        B.bnr_bwd_fused(desc, x, bn1, wd, src, dw, dga, dbe, dy)
+        torch.cuda.synchronize()
+        dz = P.conv_dgrad(g, wt.astype(np.float64), (h, w)).reshape(m, ci)
+        dyr = P.relu_bwd(dz, y1)
+        amb = relu_ambiguous(y1, bf16)
+        assert_close(name + " dy", host(dy).reshape(m, ci), dyr, rtol, exclude=amb, max_excluded_frac=1e-2)
+        assert_close(name + " dW", host(dw), P.conv_wgrad(z, g, k), rtol)
+        # the sums are of the dy that was stored
+        d64, xh = host(dy).reshape(m, ci), (x64.reshape(m, ci) - host(bn1.mean)) * host(bn1.rstd)
+        for s, got, t in (("dbeta", dbe, d64), ("dgamma", dga, d64 * xh)):
+            bound = 1e-5 * np.abs(t).sum(0) + 1e-6
+            assert np.all(np.abs(host(got) - t.sum(0)) <= bound), name + " " + s
+
+
+@pytest.mark.parametrize("n,h,w,ci,co", [
+    (2, 1, 1, 32, 32),          # one pixel: every row a wrap of the padded grid
+    (9, 2, 1, 8, 136),          # output channels past the persistent kernel (row-tile kernel)
+    (3, 3, 5, 96, 24),          # three 32-channel K slices (a zero fourth one), a ragged N slice
+    (5, 2, 3, 72, 32),          # K slices cut at 8 channels
+    (1, 61, 61, 64, 64),        # widest rows: the longest window of the input ring
+    (2, 7, 61, 32, 128),        # the same with four N slices
+    (3, 37, 2, 128, 8),         # narrow rows: many rows of the padded grid in a tile
+    (4, 13, 9, 48, 40),         # two K and two N slices, ragged
+    (2, 9, 30, 24, 96),         # one K slice, a ragged fourth N slice
+    (40, 14, 14, 128, 32),      # several tiles per workgroup, ranges that cross images
+    (1, 300, 2, 32, 64),        # tall images
+])
+def test_conv3x3_tiles_bf16(B, n, h, w, ci, co):
+    _layer(B, True, 3, n, h, w, ci, co, pad_in=8, pad_out=8)
+
+
+def test_conv3x3_nan_and_inf_stay_local(B):
+    """A NaN input is dropped by the ReLU (max(NaN, 0) = 0), an infinite one
+    reaches exactly the 3x3 outputs that read it; padding rows of the input
+    ring are zeros whatever their neighbours hold."""
+    n, h, w, ci, co = 2, 9, 9, 64, 32
+    x = torch.zeros((n, h, w, ci), dtype=torch.bfloat16, device="cuda")
+    x[0, 0, 8, 3] = float("nan")
+    x[1, 4, 0, 5] = float("inf")
+    ones, zeros = torch.ones(ci, device="cuda"), torch.zeros(ci, device="cuda")
+    bn = B.BN(ones.clone(), zeros.clone(), 1e-5, zeros.clone(), ones.clone(), ones.clone())
+    wt = torch.ones((3, 3, ci, co), dtype=torch.bfloat16, device="cuda")
+    out = torch.empty((n, h, w, co), dtype=torch.bfloat16, device="cuda")
+    B.bnr_bn_relu_conv_fwd(B.desc_for(x, out, 3, n, h, w), x, bn, wt, out)
+    torch.cuda.synchronize()
+    want = torch.zeros((n, h, w))
+    want[1, 3:6, 0:2] = float("inf")
+    got = out.float().cpu()
+    assert bool((got == want[..., None]).all())
