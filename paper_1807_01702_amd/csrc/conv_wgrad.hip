@@ -590,19 +590,235 @@ __global__ __launch_bounds__(kThreads, (TAPS == 3 && COT == 64) ? 1 : 2) void k_
                 }
 }
 
-// ------------------------------------------------------------- launchers ---
-static bool wgrad_tr_ok(int dtype, int64_t m, int h, int w, int64_t x_ldc, int64_t g_ldc, int64_t gx_ldc, int k)
+// ---------------------------------------------------------------------------
+// float32 weight gradient.  The same plan as k_wgrad_tr: both operands staged
+// row-major as they arrive, after the prologue transform, the nine taps of a
+// 3x3 row offsets into the staged Z.  A 16x16x4 float32 fragment takes one
+// value per lane (channel lane % 16, position lane / 16), a plain 4-byte read
+// of a row-major tile; row pitches of 16 mod 64 floats put the four rows of a
+// read on different banks.  The next chunk is loaded to registers during the
+// matrix-core work.  The matrix cores bound it; the transposed staging it
+// replaces wrote and read single floats and split a 3x3 by filter rows, so G
+// was staged three times.
+template <int TAPS, int CIT, int COT, int WCI, int GS>
+__global__ __launch_bounds__(kThreads, 2) void k_wgrad_f32(WgradParams p, WgTrPlan pl)
 {
-    if (dtype != DT_BF16 || (k == 3 && w > kWgMaxW3)) return false;
-    const int64_t lim = (int64_t)1 << 31;
-    return (m * x_ldc) * 2 < lim && (m * g_ldc) * 2 < lim && (m * gx_ldc) * 2 < lim && h >= 1 && w >= 1;
+    using M = Mfma<float>;
+    constexpr int VEC = 4, WCO = 4 / WCI;
+    constexpr int RB = CIT / 16 / WCI, CB = COT / 16 / WCO;
+    constexpr int ZP = CIT + 16, GP = COT + 16;                   // LDS row pitches (floats)
+    constexpr int VZ = CIT / VEC, VG = COT / VEC;                 // vectors per staged row
+    constexpr int KQMAX = TAPS == 3 ? kWfKQ3 : kWfKQ1;
+    constexpr int ZRMAX = TAPS == 3 ? KQMAX + 2 * (kWgMaxW3 + 2) + 2 : KQMAX;
+    constexpr int RZ = kThreads / VZ, RG = kThreads / VG;         // rows per pass
+    constexpr int NZ = (ZRMAX + RZ - 1) / RZ, NG = (KQMAX + RG - 1) / RG;
+    constexpr int NGX = GS == GB_BNGRAD ? NG : 1;
+    static_assert(WCI * WCO == 4 && RB >= 1 && CB >= 1 && ZP % 64 % 32 == 16 && GP % 64 % 32 == 16, "layout");
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *Zs = reinterpret_cast<float *>(smem);                  // [zrows + 1][ZP]
+    float *Gs = Zs + (size_t)(pl.zrows + 1) * ZP;                 // [KQ + 1][GP]
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wci = wave % WCI, wco = wave / WCI, q4 = lane >> 4, l16 = lane & 15;
+    const int n_out = pl.ci_tiles * pl.co_tiles;
+    const int lid = xcd_remap(blockIdx.x, gridDim.x);
+    const int ot = lid % n_out, split = lid / n_out;
+    const int ci0 = ot / pl.co_tiles * CIT, co0 = ot % pl.co_tiles * COT;
+    const int C_in = p.c_in, C_out = p.c_out, H = p.h, W = p.w;
+    const int m = (int)p.m, PW = pl.PW, KQ = pl.KQ, ZR = pl.zrows;
+
+    // this thread's channel vectors are the same in every row it stages: their
+    // parameters in registers, all loads in flight together
+    const int vz = tid % VZ, vg = tid % VG, rz0 = tid / VZ, rg0 = tid / VG;
+    const int cz = ci0 + vz * VEC, cg = co0 + vg * VEC;
+    const bool zc_ok = cz < C_in, gc_ok = cg < C_out;
+    float za[VEC], zb[VEC], zk[VEC], ga[VEC], gb[VEC], gc[VEC], gk[VEC];
+    #pragma unroll
+    for (int e = 0; e < VEC; e++) {
+        za[e] = 1.f; zb[e] = 0.f; zk[e] = 0.f;
+        ga[e] = 1.f; gb[e] = gc[e] = gk[e] = 0.f;
+    }
+    if (p.a_mode == 1 && zc_ok) {
+        #pragma unroll
+        for (int e = 0; e < VEC; e++) {
+            bn_coef(p.a_gamma[cz + e], p.a_beta[cz + e], p.a_mean[cz + e], p.a_rstd[cz + e], za[e], zb[e]);
+            zk[e] = bn_centre<float>(p.a_ctr, cz + e);
+        }
+    }
+    if (GS == GB_BNGRAD && gc_ok) {
+        #pragma unroll
+        for (int e = 0; e < VEC; e++) {
+            deferred_coef(p.g_split, cg + e, 1.0f / (float)m, p.g_gamma, p.g_mean, p.g_rstd, p.g_dgamma, p.g_dbeta,
+                          p.g_alpha, p.g_betap, ga[e], gb[e], gc[e]);
+            gk[e] = bn_centre<float>(p.g_ctr, cg + e);
+        }
+    }
+    // raw-buffer views (launcher: every span below 2^31 bytes)
+    const int xl = (int)p.x_ldc, gl = (int)p.g_ldc, gxl = (int)p.gx_ldc;
+    const __amdgpu_buffer_rsrc_t xbuf = buf_view(p.x, (uint32_t)(((int64_t)(m - 1) * xl + C_in) * 4));
+    const int gpix = GS == GB_POOLUP ? m / 4 : m;
+    const __amdgpu_buffer_rsrc_t gbuf = buf_view(p.g, (uint32_t)(((int64_t)(gpix - 1) * gl + C_out) * 4));
+    const __amdgpu_buffer_rsrc_t gxbuf = buf_view(GS == GB_BNGRAD ? p.gx : p.g,
+                                                  GS == GB_BNGRAD ? (uint32_t)(((int64_t)(m - 1) * gxl + C_out) * 4) : 0u);
+
+    // staged row -> image row offset r and pixel offset r W + col - 1, split
+    // once (kNever: a row that is never a pixel)
+    constexpr int kNever = -(1 << 28);
+    int zrr[NZ], zro[NZ], grr[NG], gro[NG];
+    #pragma unroll
+    for (int j = 0; j < NZ; j++) {
+        const int row = rz0 + j * RZ;
+        zrr[j] = row < ZR ? 0 : kNever; zro[j] = row;
+        if (TAPS == 3) {
+            const int q = row - (PW + 1), r = (q + 2 * PW) / PW - 2, col = q - r * PW;
+            zrr[j] = row < ZR && col >= 1 && col <= W ? r : kNever;
+            zro[j] = r * W + col - 1;
+        }
+    }
+    #pragma unroll
+    for (int j = 0; j < NG; j++) {
+        const int row = rg0 + j * RG;
+        grr[j] = row < KQ ? 0 : kNever; gro[j] = row;
+        if (TAPS == 3) {
+            const int r = row / PW, col = row - r * PW;
+            grr[j] = row < KQ && r < pl.R && col >= 1 && col <= W ? r : kNever;
+            gro[j] = r * W + col - 1;
+        }
+    }
+    // (1x1: pixel base + row, below m; 3x3: image row h0 + r, inside the image)
+    auto valid = [&](int base, int h0, int r, int o) __attribute__((always_inline)) -> bool {
+        return TAPS == 3 ? (unsigned)(h0 + r) < (unsigned)H : ((r == 0) & (base + o < m));
+    };
+    vec16 zr[NZ], gr[NG], gx[NGX];
+    auto load_chunk = [&](int base, int h0) __attribute__((always_inline)) {
+        #pragma unroll
+        for (int j = 0; j < NZ; j++)
+            zr[j] = bld16(xbuf, (valid(base, h0, zrr[j], zro[j]) & zc_ok) ? (uint32_t)((base + zro[j]) * xl + cz) * 4u : kBufOff);
+        #pragma unroll
+        for (int j = 0; j < NG; j++) {
+            const bool ok = valid(base, h0, grr[j], gro[j]) & gc_ok;
+            int q = base + gro[j];
+            if (GS == GB_POOLUP) {
+                const int qi = ok ? q : 0, im = qi / (H * W), rem = qi - im * H * W, y = rem / W, xx = rem - y * W;
+                q = (im * (H / 2) + y / 2) * (W / 2) + xx / 2;
+            }
+            gr[j] = bld16(gbuf, ok ? (uint32_t)(q * gl + cg) * 4u : kBufOff);
+            if (GS == GB_BNGRAD) gx[j < NGX ? j : 0] = bld16(gxbuf, ok ? (uint32_t)(q * gxl + cg) * 4u : kBufOff);
+        }
+    };
+    // (rows that are no pixel are zeros; rows past the staged range go to a junk row)
+    auto store_chunk = [&](int base, int h0) __attribute__((always_inline)) {
+        #pragma unroll
+        for (int j = 0; j < NZ; j++) {
+            const bool ok = valid(base, h0, zrr[j], zro[j]) & zc_ok;
+            float f[VEC];
+            Elem<float>::unpack(zr[j], f);
+            #pragma unroll
+            for (int e = 0; e < VEC; e++) {
+                const float t = p.a_mode == 1 ? bn_lin(f[e] - zk[e], za[e], zb[e]) : f[e];
+                f[e] = ok && (p.a_mode == 0 || t > 0.f) ? t : 0.f;
+            }
+            const int row = rz0 + j * RZ;
+            *reinterpret_cast<vec16 *>(Zs + (row < ZR ? row : ZR) * ZP + vz * VEC) = Elem<float>::pack(f);
+        }
+        #pragma unroll
+        for (int j = 0; j < NG; j++) {
+            const bool ok = valid(base, h0, grr[j], gro[j]) & gc_ok;
+            float f[VEC];
+            Elem<float>::unpack(gr[j], f);
+            if (GS == GB_BNGRAD) {
+                float x[VEC];
+                Elem<float>::unpack(gx[j < NGX ? j : 0], x);
+                #pragma unroll
+                for (int e = 0; e < VEC; e++) {
+                    const float d = __builtin_fmaf(ga[e], f[e], __builtin_fmaf(gb[e], x[e] - gk[e], gc[e]));
+                    f[e] = ok ? d : 0.f;
+                }
+            } else if (GS == GB_POOLUP) {
+                #pragma unroll
+                for (int e = 0; e < VEC; e++) f[e] *= 0.25f;
+            }
+            const int row = rg0 + j * RG;
+            *reinterpret_cast<vec16 *>(Gs + (row < KQ ? row : KQ) * GP + vg * VEC) = Elem<float>::pack(f);
+        }
+    };
+
+    f32x4 acc[TAPS * TAPS][RB][CB];
+    #pragma unroll
+    for (int t = 0; t < TAPS * TAPS; t++)
+        #pragma unroll
+        for (int rb = 0; rb < RB; rb++)
+            #pragma unroll
+            for (int cb = 0; cb < CB; cb++) acc[t][rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // chunk positions: 1x1, first pixel; 3x3, first row h0 of an image and its first pixel
+    const int64_t ch0 = (int64_t)split * pl.chunks_per_split;
+    const int nch = (int)(min(pl.nchunks, ch0 + pl.chunks_per_split) - ch0);
+    int img = TAPS == 3 ? (int)(ch0 / pl.chunks_per_image) : 0;
+    int h0 = TAPS == 3 ? (int)(ch0 - (int64_t)img * pl.chunks_per_image) * pl.R : 0;
+    int base = TAPS == 3 ? (img * H + h0) * W : (int)(ch0 * KQMAX);
+    const float *zl = Zs + q4 * ZP + wci * RB * 16 + l16, *gl_ = Gs + q4 * GP + wco * CB * 16 + l16;
+    if (nch > 0) load_chunk(base, h0);
+    for (int ch = 0; ch < nch; ch++) {
+        store_chunk(base, h0);
+        if (TAPS == 3) {
+            h0 += pl.R;
+            if (h0 >= H) { h0 = 0; img++; }
+            base = (img * H + h0) * W;
+        } else {
+            base += KQMAX;
+        }
+        __syncthreads();
+        if (ch + 1 < nch) load_chunk(base, h0);
+        for (int kq = 0; kq < KQ; kq += M::KSTEP) {
+            float b[CB];
+            #pragma unroll
+            for (int cb = 0; cb < CB; cb++) b[cb] = gl_[kq * GP + cb * 16];
+            #pragma unroll
+            for (int t = 0; t < TAPS * TAPS; t++) {
+                const int toff = TAPS == 3 ? (t / 3) * PW + (t % 3) : 0;
+                #pragma unroll
+                for (int rb = 0; rb < RB; rb++) {
+                    const float a = zl[(kq + toff) * ZP + rb * 16];
+                    #pragma unroll
+                    for (int cb = 0; cb < CB; cb++) M::mma(acc[t][rb][cb], a, b[cb]);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // ---- partial tile (or dW directly when there is one split) ----
+    float *dst = pl.splits == 1 ? p.dw : p.part + (int64_t)split * p.k * p.k * C_in * C_out;
+    #pragma unroll
+    for (int t = 0; t < TAPS * TAPS; t++)
+        #pragma unroll
+        for (int rb = 0; rb < RB; rb++)
+            #pragma unroll
+            for (int cb = 0; cb < CB; cb++)
+                #pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const int ci = ci0 + (wci * RB + rb) * 16 + 4 * q4 + i, co = co0 + (wco * CB + cb) * 16 + l16;
+                    if (ci < C_in && co < C_out) dst[((int64_t)t * C_in + ci) * C_out + co] = acc[t][rb][cb][i];
+                }
+}
+
+// ------------------------------------------------------------- launchers ---
+// Every operand span below 2^31 bytes (raw-buffer offsets): the row-major
+// kernels of either type; larger tensors take k_wgrad.
+static bool wgrad_spans_fit(int dtype, int64_t m, int h, int w, int64_t x_ldc, int64_t g_ldc, int64_t gx_ldc, int k)
+{
+    if (k == 3 && w > kWgMaxW3) return false;
+    const int64_t lim = (int64_t)1 << 31, es = dtype == DT_BF16 ? 2 : 4;
+    return (m * x_ldc) * es < lim && (m * g_ldc) * es < lim && (m * gx_ldc) * es < lim && h >= 1 && w >= 1;
 }
 
 size_t wgrad_ws_bytes(int dtype, int64_t m, int n, int h, int w, int c_in, int c_out, int k)
 {
     const WgradPlan pl = wgrad_plan(m, n, h, w, c_in, c_out, k, dtype == DT_BF16 ? 2 : 4);
     const WgTrPlan tp = wgrad_tr_plan(m, n, h, w, c_in, c_out, k);
-    const int64_t s = dtype == DT_BF16 ? (pl.splits > tp.splits ? pl.splits : tp.splits) : pl.splits;
+    const int64_t rs = dtype == DT_BF16 ? tp.splits : wgrad_f32_plan(m, n, h, w, c_in, c_out, k).splits;
+    const int64_t s = pl.splits > rs ? pl.splits : rs;
     if (s <= 1) return 0;
     return (size_t)s * k * k * c_in * c_out * sizeof(float);
 }
@@ -641,6 +857,35 @@ static hipError_t dispatch_wgrad_tr(const WgradParams &p, const WgTrPlan &pl, hi
     return run_wgrad_tr<1, 128, 128, 2>(p, pl, s);
 }
 
+template <int TAPS, int CIT, int COT, int WCI>
+static hipError_t run_wgrad_f32(const WgradParams &p, const WgTrPlan &pl, hipStream_t s)
+{
+    const int64_t blocks = (int64_t)pl.ci_tiles * pl.co_tiles * pl.splits;
+    const size_t lds = ((size_t)(pl.zrows + 1) * (CIT + 16) + (size_t)(pl.KQ + 1) * (COT + 16)) * sizeof(float);
+    const double m = (double)p.m;
+    double g = m * p.c_out;
+    if (p.gsrc == GB_BNGRAD) g *= 2.0;
+    if (p.gsrc == GB_POOLUP) g /= 4.0;
+    const double dwb = (double)p.k * p.k * p.c_in * p.c_out;
+    TraceScope tr(KC_WGRAD, TAPS == 3 ? KID_WGRAD_3X3 : KID_WGRAD_1X1, s, 4.0 * (m * p.c_in + g) + 4.0 * dwb,
+                  2.0 * m * dwb);
+    if (p.gsrc == GB_BNGRAD)
+        hipLaunchKernelGGL((k_wgrad_f32<TAPS, CIT, COT, WCI, GB_BNGRAD>), dim3((unsigned)blocks), dim3(kThreads), lds, s, p, pl);
+    else if (p.gsrc == GB_POOLUP)
+        hipLaunchKernelGGL((k_wgrad_f32<TAPS, CIT, COT, WCI, GB_POOLUP>), dim3((unsigned)blocks), dim3(kThreads), lds, s, p, pl);
+    else
+        hipLaunchKernelGGL((k_wgrad_f32<TAPS, CIT, COT, WCI, GB_DENSE>), dim3((unsigned)blocks), dim3(kThreads), lds, s, p, pl);
+    return hipGetLastError();
+}
+
+static hipError_t dispatch_wgrad_f32(const WgradParams &p, const WgTrPlan &pl, hipStream_t s)
+{
+    if (pl.k == 3) return pl.cot == 32 ? run_wgrad_f32<3, 32, 32, 2>(p, pl, s) : run_wgrad_f32<3, 32, 64, 2>(p, pl, s);
+    if (pl.cot == 32) return run_wgrad_f32<1, 64, 32, 4>(p, pl, s);
+    if (pl.cot == 64) return run_wgrad_f32<1, 64, 64, 2>(p, pl, s);
+    return run_wgrad_f32<1, 64, 128, 2>(p, pl, s);
+}
+
 template <typename T, int TAPS, int COT, int WR, int WC>
 static hipError_t run_wgrad(const WgradParams &p, const WgradPlan &pl, hipStream_t s)
 {
@@ -673,10 +918,12 @@ hipError_t launch_wgrad(const WgradParams &p, hipStream_t s, int64_t *splits_out
                                 (p.g_split ? (!p.g_alpha || !p.g_betap) : (!p.g_gamma || !p.g_dbeta || !p.g_dgamma))))
         return hipErrorInvalidValue;
     if (p.k == 3 && p.w > kWgMaxW3) return hipErrorInvalidValue;
-    if (wgrad_tr_ok(p.dtype, p.m, p.h, p.w, p.x_ldc, p.g_ldc, p.gsrc == GB_BNGRAD ? p.gx_ldc : 0, p.k)) {
-        const WgTrPlan tp = wgrad_tr_plan(p.m, p.n, p.h, p.w, p.c_in, p.c_out, p.k);
+    if (wgrad_spans_fit(p.dtype, p.m, p.h, p.w, p.x_ldc, p.g_ldc, p.gsrc == GB_BNGRAD ? p.gx_ldc : 0, p.k)) {
+        const bool bf = p.dtype == DT_BF16;
+        const WgTrPlan tp = bf ? wgrad_tr_plan(p.m, p.n, p.h, p.w, p.c_in, p.c_out, p.k)
+                               : wgrad_f32_plan(p.m, p.n, p.h, p.w, p.c_in, p.c_out, p.k);
         if (tp.splits > 1 && (!p.part || !p.red)) return hipErrorInvalidValue;
-        const hipError_t e = dispatch_wgrad_tr(p, tp, s);
+        const hipError_t e = bf ? dispatch_wgrad_tr(p, tp, s) : dispatch_wgrad_f32(p, tp, s);
         if (splits_out) *splits_out = tp.splits;
         if (e != hipSuccess || tp.splits <= 1 || splits_out) return e;
         return launch_sum_partials(p.part, tp.splits, (int64_t)p.k * p.k * p.c_in * p.c_out, p.dw, p.red, s);

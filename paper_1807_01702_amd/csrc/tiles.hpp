@@ -163,4 +163,50 @@ inline WgTrPlan wgrad_tr_plan(int64_t m, int n, int h, int w, int c_in, int c_ou
     return p;
 }
 
+// ---- float32 weight gradient --------------------------------------------
+// Both operands staged row-major (one row per K position); 1x1: 64 input x
+// COT output channels, chunks of 32 pixels; 3x3: 32 input x COT output
+// channels and all nine taps, chunks of R image rows of PW = W + 2 padded
+// positions (KQ <= 64 of them), Z rows with a halo as in wgrad_tr_plan.  The
+// split count aims at two workgroups per CU; partial tiles stay below the
+// operand bytes, or below kWgTrSmallPartBytes for small operands (as there).
+constexpr int kWfKQ1 = 32, kWfKQ3 = 64;
+inline WgTrPlan wgrad_f32_plan(int64_t m, int n, int h, int w, int c_in, int c_out, int k)
+{
+    WgTrPlan p;
+    p.k = k;
+    p.cit = k == 3 ? 32 : 64;
+    p.cot = c_out <= 32 ? 32 : (c_out <= 64 || k == 3 ? 64 : 128);
+    p.ci_tiles = (int)ceil_div(c_in, p.cit);
+    p.co_tiles = (int)ceil_div(c_out, p.cot);
+    if (k == 3) {
+        p.PW = w + 2;
+        p.R = kWfKQ3 / p.PW < 1 ? 1 : kWfKQ3 / p.PW;
+        if (p.R > h) p.R = h;
+        p.KQ = (int)ceil_div((int64_t)p.R * p.PW, 4) * 4;
+        p.zrows = p.KQ + 2 * p.PW + 2;
+        p.chunks_per_image = ceil_div(h, p.R);
+        p.nchunks = (int64_t)n * p.chunks_per_image;
+    } else {
+        p.PW = 0;
+        p.R = 0;
+        p.KQ = kWfKQ1;
+        p.zrows = kWfKQ1;
+        p.chunks_per_image = 0;
+        p.nchunks = ceil_div(m, kWfKQ1);
+    }
+    int64_t s = ceil_div(512, (int64_t)p.ci_tiles * p.co_tiles);
+    const int64_t dw_bytes = (int64_t)k * k * c_in * c_out * 4;
+    int64_t in_bytes = m * (int64_t)(c_in + c_out) * 4;
+    if (in_bytes < kWgTrSmallPartBytes) in_bytes = kWgTrSmallPartBytes;
+    int64_t cap = in_bytes / (dw_bytes > 0 ? dw_bytes : 1);
+    if (cap < 1) cap = 1;
+    if (s > cap) s = cap;
+    if (s > p.nchunks) s = p.nchunks;
+    if (s < 1) s = 1;
+    p.chunks_per_split = ceil_div(p.nchunks, s);
+    p.splits = ceil_div(p.nchunks, p.chunks_per_split);
+    return p;
+}
+
 }  // namespace bnr
