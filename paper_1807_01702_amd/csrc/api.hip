@@ -301,6 +301,13 @@ bnr_status launch_conv_any(RowsParams &rp, const bnr_conv_desc *d, const void *w
         TRY_HIP(launch_conv3x3(rp, s), transpose ? "conv data gradient" : "conv forward");
         return BNR_OK;
     }
+    if (conv_f32_supported(rp)) {
+        rp.wraw = w;
+        rp.wtrans = transpose;
+        *rows = rows_mtiles(rp.dtype, rp.taps, rp.m, rp.N);
+        TRY_HIP(launch_conv_f32(rp, s), transpose ? "conv data gradient" : "conv forward");
+        return BNR_OK;
+    }
     if (rows_direct_weights(rp.dtype, rp.taps, rp.m, rp.K, rp.N, rp.a_ldc, rp.a2_ldc, rp.pro, rp.side != nullptr)) {
         rp.wdirect = 1;                 // bf16 1x1: the tiled kernel reads the caller's weights, no packing
         rp.wraw = w;

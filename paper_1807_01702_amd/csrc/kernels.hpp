@@ -155,6 +155,10 @@ bool conv3x3_supported(int dtype, int K, int N, int H, int W);
 int64_t conv3x3_partial_rows(int64_t m);      // statistics partial rows it writes
 hipError_t launch_conv3x3(const RowsParams &p, hipStream_t s);
 
+// ---- float32 CONV on the caller's weights (no packing); statistics partial rows: rows_mtiles ----
+bool conv_f32_supported(const RowsParams &p);
+hipError_t launch_conv_f32(const RowsParams &p, hipStream_t s);
+
 // ---- weight gradient -------------------------------------------------------
 enum { GB_DENSE = 0, GB_BNGRAD = 1, GB_POOLUP = 2 };
 struct WgradParams {
