@@ -181,14 +181,14 @@ def view(t):
     """(data pointer, pixels, channels, pixel stride) of a channel view."""
     if t.dim() < 2 or t.stride(-1) != 1:
         raise ValueError("view needs a unit-stride channel dimension")
-    ldc = t.stride(-2)
-    for i in range(t.dim() - 2):
-        if t.shape[i] > 1 and t.stride(i) != t.stride(i + 1) * t.shape[i + 1]:
+    shape, stride = t.shape, t.stride()
+    for i in range(len(shape) - 2):
+        if shape[i] > 1 and stride[i] != stride[i + 1] * shape[i + 1]:
             raise ValueError("leading dimensions of a view must collapse to one pixel stride")
     m = 1
-    for s in t.shape[:-1]:
+    for s in shape[:-1]:
         m *= s
-    return t.data_ptr(), m, t.shape[-1], ldc
+    return t.data_ptr(), m, shape[-1], stride[-2]
 
 
 def _ptr(t):
@@ -196,7 +196,13 @@ def _ptr(t):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream of the current device as a raw handle, without building
+    # the torch.cuda.Stream object around it (4 us a call, a quarter of a small
+    # call's host time)
+    return _raw_stream(_current_device())
+
+
+_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
 
 
 _ws_cache = {}
@@ -206,7 +212,9 @@ def workspace(nbytes, device=None, slot=0):
     """Grow-only per-device workspace (device memory from torch); calls that
     may be in flight at the same time (on different streams) use different
     slots."""
-    dev = torch.device(device) if device is not None else torch.device("cuda", torch.cuda.current_device())
+    dev = device
+    if type(dev) is not torch.device:
+        dev = torch.device(dev) if dev is not None else torch.device("cuda", torch.cuda.current_device())
     cur = _ws_cache.get((dev, slot))
     if cur is None or cur.numel() < nbytes:
         cur = torch.empty(max(int(nbytes), 256) + 256, dtype=torch.uint8, device=dev)
@@ -265,9 +273,11 @@ class BN:
         return b
 
     def struct(self):
-        return BNStruct(_ptr(self.gamma), _ptr(self.beta), _ptr(self.mean), _ptr(self.var), _ptr(self.rstd),
-                        self.eps, _ptr(self.shift), _ptr(self.running_mean), _ptr(self.running_var),
-                        self.momentum, _ptr(self.mean_lo))
+        s = BNStruct(_ptr(self.gamma), _ptr(self.beta), _ptr(self.mean), _ptr(self.var), _ptr(self.rstd), self.eps)
+        if not (self.mean_lo is None and self.shift is None and self.running_mean is None and self.running_var is None):
+            s.shift, s.running_mean, s.running_var = _ptr(self.shift), _ptr(self.running_mean), _ptr(self.running_var)
+            s.momentum, s.mean_lo = self.momentum, _ptr(self.mean_lo)
+        return s
 
 
 def conv_desc(n, h, w, c_in, c_out, k, in_ldc, out_ldc, dtype):

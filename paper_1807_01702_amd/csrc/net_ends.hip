@@ -72,6 +72,8 @@ __device__ __forceinline__ void stem_stage_image(const StemParams &p, const Stem
 
 }  // namespace
 
+static_assert(kStemRows == 2, "the weight gradient's row of a pixel is one comparison");
+
 // --------------------------------------------------------------------------
 // First CONV forward (bf16): out[n][oh][ow][co] = sum_{kh,kw,ci} img[n][2oh-3+kh]
 // [2ow-3+kw][ci] w[kh][kw][ci][co], optional per-channel sum / sum of squares
@@ -285,35 +287,81 @@ __global__ __launch_bounds__(kThreads, 2) void k_stem_wgrad(StemParams p)
         #pragma unroll
         for (int cb = 0; cb < 4; cb++) acc[ki][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // Register stage of one item: image pixel slots q = tid + j 256 of the
+    // kSIR x RPX staged pixels, gradient slots (pixel tid / 8 + 32 j, channel
+    // vector tid % 8).  Their rows and columns are split once; an item is a
+    // base pointer and range tests (loads at a clamped position, zeroed when
+    // they are written to LDS).
+    constexpr int NI = (kSIR * (kStemMaxW + 6) + kThreads - 1) / kThreads, NG = (kStemRows * (kStemMaxW / 2) + 31) / 32;
+    constexpr int kNever = -(1 << 28);
+    int ir[NI], io[NI];
+    #pragma unroll
+    for (int j = 0; j < NI; j++) {
+        const int q = tid + j * kThreads, r = q / RPX, iw = q - r * RPX - kStemPad;
+        ir[j] = q < kSIR * RPX && iw >= 0 && iw < p.w ? r : kNever;
+        io[j] = r * p.w + iw;
+    }
+    const uint32_t keep_lo = p.c_in >= 2 ? 0xffffffffu : 0x0000ffffu;
+    const uint32_t keep_hi = p.c_in >= 4 ? 0xffffffffu : (p.c_in == 3 ? 0x0000ffffu : 0u);
+    const int c8 = (tid & 7) * 8, gp0 = tid >> 3;
+    float gA[8], gB[8], gC[8];
+    if (GS == GB_BNGRAD) { lds_f8(gco + c8, gA); lds_f8(gco + kStemCout + c8, gB); lds_f8(gco + 2 * kStemCout + c8, gC); }
+    const uint2 *img = reinterpret_cast<const uint2 *>(p.img);
     const bf16_t *gsrc = reinterpret_cast<const bf16_t *>(p.g);
     const bf16_t *gx = reinterpret_cast<const bf16_t *>(p.gx);
-    for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
-        const StemItem t = stem_item(p, it);
-        stem_stage_image(p, t, img_s, tid);
+    const int g_ld = GS == GB_BNGRAD ? kStemCout : (int)p.g_ldc, gx_ld = (int)p.gx_ldc;
+    uint2 vi[NI];
+    vec16 vg[NG], vx[GS == GB_BNGRAD ? NG : 1];
+    auto load_item = [&](const StemItem &t) __attribute__((always_inline)) {
+        const uint2 *base = img + (int64_t)t.n * p.h * p.w;
+        const int ih0 = 2 * t.oh0 - kStemPad, o0 = ih0 * p.w;
+        #pragma unroll
+        for (int j = 0; j < NI; j++) vi[j] = base[(unsigned)(ih0 + ir[j]) < (unsigned)p.h ? o0 + io[j] : 0];
         const int64_t q0 = ((int64_t)t.n * p.ho + t.oh0) * wo;
-        for (int v = tid; v < PP * 8; v += kThreads) {
-            const int pp = v >> 3, c8 = v & 7;
-            vec16 o = zero16();
-            if (pp < t.pv) {
-                const int64_t q = q0 + pp;
-                if (GS == GB_BNGRAD) {
-                    float d[8], x[8];
-                    Elem<bf16_t>::unpack(ldg16(gsrc + q * kStemCout + c8 * 8), d);
-                    Elem<bf16_t>::unpack(ldg16(gx + q * p.gx_ldc + c8 * 8), x);
-                    #pragma unroll
-                    for (int e = 0; e < 8; e++) {
-                        const int c = c8 * 8 + e;
-                        d[e] = __builtin_fmaf(gco[c], d[e], __builtin_fmaf(gco[kStemCout + c], x[e],
-                                                                            gco[2 * kStemCout + c]));
-                    }
-                    o = Elem<bf16_t>::pack(d);
-                } else {
-                    o = ldg16(gsrc + q * p.g_ldc + c8 * 8);
-                }
-            }
-            *reinterpret_cast<vec16 *>(Gs + pp * kSPitch + c8 * 8) = o;
+        const bf16_t *gb = gsrc + q0 * g_ld + c8, *xb = gx + q0 * gx_ld + c8;
+        #pragma unroll
+        for (int j = 0; j < NG; j++) {
+            const int pp = gp0 + 32 * j < t.pv ? gp0 + 32 * j : 0;
+            vg[j] = ldg16(gb + pp * g_ld);
+            if (GS == GB_BNGRAD) vx[GS == GB_BNGRAD ? j : 0] = ldg16(xb + pp * gx_ld);
         }
+    };
+    auto store_item = [&](const StemItem &t) __attribute__((always_inline)) {
+        const int ih0 = 2 * t.oh0 - kStemPad;
+        #pragma unroll
+        for (int j = 0; j < NI; j++) {
+            const bool in = (unsigned)(ih0 + ir[j]) < (unsigned)p.h;
+            if (tid + j * kThreads < kSIR * RPX)
+                img_s[tid + j * kThreads] = make_uint2(in ? vi[j].x & keep_lo : 0u, in ? vi[j].y & keep_hi : 0u);
+        }
+        #pragma unroll
+        for (int j = 0; j < NG; j++) {
+            const int pp = gp0 + 32 * j;
+            vec16 o = vg[j];
+            if (GS == GB_BNGRAD) {
+                float d[8], x[8];
+                Elem<bf16_t>::unpack(vg[j], d);
+                Elem<bf16_t>::unpack(vx[GS == GB_BNGRAD ? j : 0], x);
+                #pragma unroll
+                for (int e = 0; e < 8; e++) d[e] = __builtin_fmaf(gA[e], d[e], __builtin_fmaf(gB[e], x[e], gC[e]));
+                o = Elem<bf16_t>::pack(d);
+            }
+            const uint32_t keep = pp < t.pv ? 0xffffffffu : 0u;
+            #pragma unroll
+            for (int e = 0; e < 4; e++) o.u[e] &= keep;
+            if (pp < PP) *reinterpret_cast<vec16 *>(Gs + pp * kSPitch + c8) = o;
+        }
+    };
+    StemItem t = stem_item(p, blockIdx.x < items ? blockIdx.x : 0);
+    if (blockIdx.x < items) load_item(t);
+    for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
+        store_item(t);
+        const int pv = t.pv;
         __syncthreads();
+        if (it + gridDim.x < items) {                    // the next item arrives during the matrix-core work
+            t = stem_item(p, it + gridDim.x);
+            load_item(t);
+        }
         for (int p0 = 0; p0 < PP; p0 += 32) {
             bf16x8 b[4];
             const bf16_t *gb = Gs + (p0 + 8 * g16 + (l16 >> 2)) * kSPitch + 4 * (l16 & 3);
@@ -321,9 +369,9 @@ __global__ __launch_bounds__(kThreads, 2) void k_stem_wgrad(StemParams p)
             for (int cb = 0; cb < 4; cb++) b[cb] = tr_pair(gb + cb * 16, gb + 4 * kSPitch + cb * 16);
             // patch rows of this lane's two pixels (padding pixels read pixel 0)
             int plo = p0 + 8 * g16 + (l16 >> 2), phi = plo + 4;
-            if (plo >= t.pv) plo = 0;
-            if (phi >= t.pv) phi = 0;
-            const int rlo = plo / wo, rhi = phi / wo;
+            if (plo >= pv) plo = 0;
+            if (phi >= pv) phi = 0;
+            const int rlo = plo >= wo ? 1 : 0, rhi = phi >= wo ? 1 : 0;     // (items of two output rows)
             const int blo = 2 * rlo * RPX + 2 * (plo - rlo * wo) + (l16 & 3);
             const int bhi = 2 * rhi * RPX + 2 * (phi - rhi * wo) + (l16 & 3);
             #pragma unroll
@@ -503,161 +551,225 @@ __global__ __launch_bounds__(kThreads) void k_maxpool_fwd(MaxPoolParams p, int64
     }
 }
 
-// Backward of k_maxpool_fwd.  Item = (image, input rows 2j and 2j+1), whose
-// pooling windows are those of output rows j and j+1.  Phase 1 writes, per
-// window of those two output rows and channel, the tap index of its first
-// maximum (as in the forward pass) to LDS; phase 2 gives every input pixel of
-// the two rows the sum of the gradients of the windows (in row-major window
-// order) whose maximum it is.  With BN the result dz is the gradient of the
-// ReLU output: dy = dz [y > 0] (y recomputed from x) is stored and the BN
-// reductions sum(dy), sum(dy * xhat) of the stored dy are accumulated; without
-// BN dz is stored.  The per-thread channel vector is fixed (256 is a multiple
-// of the vectors per pixel), so the sums stay in registers across items.
+// Backward of k_maxpool_fwd: every input pixel of the image gets the sum of the
+// gradients of the windows (in row-major window order) whose first maximum it
+// is.  With BN that is the gradient of the ReLU output: dy = dz [y > 0] (y
+// recomputed from x) is stored and the BN reductions sum(dy), sum(dy * xhat) of
+// the stored dy are accumulated; without BN dz is stored.
+// A workgroup takes chunks of consecutive row pairs of
+// one image; thread (ow, v) owns channel vector v of window column ow and of
+// the input columns 2 ow, 2 ow + 1.  Per window row it reads two input rows
+// (the third is carried: every input row is reduced over its three columns
+// once, "first maximum" kept as value and column), so the first-maximum tap of
+// every window, the gradients routed to a pixel block and the block's BN input
+// all come from registers, except what the right-hand neighbour's windows
+// hold, which goes through LDS (three row buffers, one barrier per row).
+// A value wins over an earlier one only if it is greater (NaN never wins).
+// What bounds it: instructions (about 800 per row pair and wave) next to HBM;
+// 128 images of 112 x 112 x 64: 240 us with the windows of every row pair
+// scanned twice from global memory and their codes in LDS bytes.
+constexpr int mp_threads(int vec) { return kMaxPoolMaxWo * kMaxPoolMaxC / vec; }
 template <typename T, bool BN>
-__global__ __launch_bounds__(kThreads) void k_maxpool_bwd(MaxPoolParams p)
+__global__ __launch_bounds__(mp_threads(Elem<T>::VEC), 4) void k_maxpool_bwd(MaxPoolParams p, int pairs_per_chunk,
+                                                                            int chunks_per_image, int64_t chunks)
 {
-    constexpr int VEC = Elem<T>::VEC;
-    __shared__ __align__(16) uint8_t codes[2][kMaxPoolMaxWo * kMaxPoolMaxC];
-    __shared__ float red[2][BN ? kThreads * VEC : 1];
-    __shared__ float sgn_s[kMaxPoolMaxC];                         // sign(gamma) per channel
-    const int C = p.c, h = p.h, w = p.w, ho = p.ho, wo = p.wo;
-    const int cvec = C / VEC;
-    const int tid = threadIdx.x, cv = tid % cvec;
-    const int hp = (h + 1) / 2;
-    const int64_t items = (int64_t)p.n * hp;
-    float k[VEC], b[VEC], mu[VEC], rs[VEC], kc[VEC], s1[VEC], s2[VEC];
-    #pragma unroll
-    for (int i = 0; i < VEC; i++) {
-        s1[i] = s2[i] = 0.f;
-        k[i] = 1.f; b[i] = 0.f; mu[i] = 0.f; rs[i] = 1.f; kc[i] = 0.f;
-        if (BN) {
-            const int c = cv * VEC + i;
-            const float g = p.gamma[c];
-            mu[i] = p.mean[c];
-            rs[i] = p.rstd[c];
-            kc[i] = bn_centre<T>(p.ctr, c);
-            bn_coef(g, p.beta[c], mu[i], rs[i], k[i], b[i]);
-        }
+    constexpr int VEC = Elem<T>::VEC, NTHR = mp_threads(VEC), CW = VEC / 4;      // CW: code words of a vector
+    // row buffers of the windows' gradients and codes (with a guard vector past
+    // the last column), then the partial sums
+    constexpr int LD = NTHR + 16;
+    __shared__ __align__(16) unsigned char raw[3 * LD * (16 + 4 * CW)];
+    __shared__ __align__(16) float par[4][kMaxPoolMaxC];           // sign(gamma), c0, c1, mean
+    vec16 (*g_s)[LD] = reinterpret_cast<vec16 (*)[LD]>(raw);                               // [3][LD]
+    uint32_t (*c_s)[CW][LD] = reinterpret_cast<uint32_t (*)[CW][LD]>(raw + 3 * LD * 16);   // [3][CW][LD]
+    float (*red)[NTHR * VEC] = reinterpret_cast<float (*)[NTHR * VEC]>(raw);               // [2][NTHR VEC]
+    static_assert(sizeof(raw) >= 2 * NTHR * VEC * sizeof(float), "partial sums");
+    const int C = p.c, h = p.h, w = p.w, ho = p.ho, wo = p.wo, cvec = C / VEC;
+    const int tid = threadIdx.x, v = tid % cvec, ow = tid / cvec;
+    const bool act = ow < wo;
+    if (tid < C) {
+        const float g = BN ? p.gamma[tid] : 1.f;
+        float c0 = 1.f, c1 = 0.f;
+        if (BN) bn_coef(g, p.beta[tid], p.mean[tid], p.rstd[tid], c0, c1);
+        par[0][tid] = g > 0.f ? 1.f : (g < 0.f ? -1.f : 0.f);
+        par[1][tid] = c0;
+        par[2][tid] = c1;
+        par[3][tid] = BN ? p.mean[tid] : 0.f;
     }
-    if (BN && tid < C) {
-        const float g = p.gamma[tid];
-        sgn_s[tid] = g > 0.f ? 1.f : (g < 0.f ? -1.f : 0.f);
-    }
+    // no window past the last column, ever: code 15 matches no tap
+    for (int i = tid; i < 3 * CW * 16; i += NTHR) c_s[i / (CW * 16)][i / 16 % CW][(int)(wo * cvec) + i % 16] = 0x0f0f0f0fu;
+    for (int i = tid; i < 3 * 16; i += NTHR) g_s[i / 16][wo * cvec + i % 16] = zero16();
     __syncthreads();
-    const T *x = reinterpret_cast<const T *>(p.x);
-    const T *gy = reinterpret_cast<const T *>(p.g);
-    T *dy = reinterpret_cast<T *>(p.y);
-    for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
-        const int64_t n = it / hp;
-        const int j = (int)(it - n * hp);
-        // phase 1: first-maximum taps of output rows j, j + 1
-        for (int t = tid; t < 2 * wo * cvec; t += kThreads) {
-            const int orow = t / (wo * cvec), rem = t - orow * wo * cvec;
-            const int ow = rem / cvec, v = rem - ow * cvec;
-            const int oh = j + orow;
-            if (oh >= ho) continue;
-            float best[VEC];
-            uint32_t code[VEC];
+    const float *sgn = par[0] + v * VEC;
+    float s1[VEC], s2[VEC], kc[VEC];
+    #pragma unroll
+    for (int e = 0; e < VEC; e++) { s1[e] = s2[e] = 0.f; kc[e] = BN ? bn_centre<T>(p.ctr, v * VEC + e) : 0.f; }
+    const T *x = reinterpret_cast<const T *>(p.x) + v * VEC;
+    const T *gy = reinterpret_cast<const T *>(p.g) + v * VEC;
+    T *dy = reinterpret_cast<T *>(p.y) + v * VEC;
+    const int cl = 2 * ow - 1 >= 0 ? 2 * ow - 1 : 0, cm = act ? 2 * ow : 0, cr = 2 * ow + 1 < w ? 2 * ow + 1 : w - 1;
+    const bool in_l = ow > 0, in_r = 2 * ow + 1 < w;
+    const int clc = act ? cl : 0, crc = act ? cr : 0;
+
+    // first maximum of an input row's three columns (value, column 0..2 in
+    // cols, four bits a channel); the vectors of columns 2 ow, 2 ow + 1 stay
+    // with the caller
+    auto row_max = [&](const vec16 &vl, const vec16 &vm, const vec16 &vr, bool in, float *best,
+                       uint32_t &cols) __attribute__((always_inline)) {
+        float l[VEC], m_[VEC], r[VEC];
+        Elem<T>::unpack(vl, l);
+        Elem<T>::unpack(vm, m_);
+        Elem<T>::unpack(vr, r);
+        cols = 0u;
+        #pragma unroll
+        for (int e = 0; e < VEC; e++) {
+            const float sg = BN ? sgn[e] : 1.f;
+            float b = -INFINITY;
+            uint32_t c = 0u;
+            const float kl = in && in_l ? sg * l[e] : -INFINITY, km = in ? sg * m_[e] : -INFINITY;
+            const float kr = in && in_r ? sg * r[e] : -INFINITY;
+            if (kl > b) b = kl;
+            if (km > b) { b = km; c = 1u; }
+            if (kr > b) { b = kr; c = 2u; }
+            best[e] = b;
+            cols |= c << (4 * e);
+        }
+    };
+
+    for (int64_t ck = blockIdx.x; ck < chunks; ck += gridDim.x) {
+        const int n = (int)(ck / chunks_per_image);
+        const int j0 = (int)(ck - (int64_t)n * chunks_per_image) * pairs_per_chunk;
+        const int hp = (h + 1) / 2, j1 = min(hp, j0 + pairs_per_chunk);
+        const T *xn = x + (int64_t)n * h * w * p.x_ldc;
+        const T *gn = gy + (int64_t)n * ho * wo * p.g_ldc;
+        T *dn = dy + (int64_t)n * h * w * C;
+        auto ldx = [&](int row, int col) __attribute__((always_inline)) {
+            const int rc = row < 0 ? 0 : (row < h ? row : h - 1);
+            return ldg16(xn + (int64_t)(rc * w + col) * p.x_ldc);
+        };
+        // the row above the chunk
+        float hb[VEC];
+        uint32_t hc;
+        {
+            const int r = 2 * j0 - 1;
+            const vec16 a = ldx(r, clc), b = ldx(r, cm), c = ldx(r, crc);
+            row_max(a, b, c, r >= 0, hb, hc);
+        }
+        vec16 xp[4], gp = zero16();                 // pixel block and gradient of the window row before
+        uint32_t cp[CW];
+        #pragma unroll
+        for (int i = 0; i < CW; i++) cp[i] = 0x0f0f0f0fu;
+        #pragma unroll
+        for (int i = 0; i < 4; i++) xp[i] = zero16();
+        for (int oh = j0; oh <= j1; oh++) {
+            // ---- window row oh: input rows 2 oh - 1 (carried), 2 oh, 2 oh + 1 ----
+            const int r0 = 2 * oh, r1 = 2 * oh + 1;
+            const bool wrow = oh < ho;
+            vec16 xa[3], xb[3];
+            xa[0] = ldx(r0, clc); xa[1] = ldx(r0, cm); xa[2] = ldx(r0, crc);
+            xb[0] = ldx(r1, clc); xb[1] = ldx(r1, cm); xb[2] = ldx(r1, crc);
+            const vec16 gw = ldg16(gn + (int64_t)((wrow ? oh : ho - 1) * wo + (act ? ow : 0)) * p.g_ldc);
+            float ba[VEC], bb[VEC];
+            uint32_t ca, cb, code[CW];
+            row_max(xa[0], xa[1], xa[2], r0 < h, ba, ca);
+            row_max(xb[0], xb[1], xb[2], r1 < h, bb, cb);
             #pragma unroll
-            for (int i = 0; i < VEC; i++) { best[i] = -INFINITY; code[i] = 0; }
-            // the nine taps' loads first at clamped positions, then the scan
-            // in tap order (as in the forward pass)
-            vec16 tv[9];
-            bool tin[9];
+            for (int i = 0; i < CW; i++) code[i] = 0u;
             #pragma unroll
-            for (int t9 = 0; t9 < 9; t9++) {
-                const int ih = 2 * oh - 1 + t9 / 3, iw = 2 * ow - 1 + t9 % 3;
-                tin[t9] = ih >= 0 && ih < h && iw >= 0 && iw < w;
-                const int ihc = ih < 0 ? 0 : (ih >= h ? h - 1 : ih), iwc = iw < 0 ? 0 : (iw >= w ? w - 1 : iw);
-                tv[t9] = ldg16(x + ((n * h + ihc) * w + iwc) * p.x_ldc + v * VEC);
+            for (int e = 0; e < VEC; e++) {
+                float b = -INFINITY;
+                uint32_t t = 0u;
+                if (hb[e] > b) { b = hb[e]; t = (hc >> (4 * e)) & 3u; }
+                if (ba[e] > b) { b = ba[e]; t = 3u + ((ca >> (4 * e)) & 3u); }
+                if (bb[e] > b) t = 6u + ((cb >> (4 * e)) & 3u);
+                code[e / 4] |= t << (8 * (e % 4));
+                hb[e] = bb[e];
             }
+            hc = cb;
             #pragma unroll
-            for (int t9 = 0; t9 < 9; t9++) {
-                if (!tin[t9]) continue;
-                float f[VEC];
-                Elem<T>::unpack(tv[t9], f);
+            for (int i = 0; i < CW; i++) code[i] = wrow && act ? code[i] : 0x0f0f0f0fu;
+            const int buf = oh % 3, pbuf = (oh + 2) % 3;
+            if (act) {
+                g_s[buf][tid] = gw;
                 #pragma unroll
-                for (int i = 0; i < VEC; i++) {
-                    const float kk = BN ? sgn_s[v * VEC + i] * f[i] : f[i];
-                    if (kk > best[i]) { best[i] = kk; code[i] = (uint32_t)t9; }
+                for (int i = 0; i < CW; i++) c_s[buf][i][tid] = code[i];
+            }
+            __syncthreads();
+            // ---- pixels of rows 2 j, 2 j + 1, columns 2 ow, 2 ow + 1 (j = oh - 1) ----
+            if (oh > j0 && act) {
+                const int j = oh - 1;
+                const vec16 gpr = g_s[pbuf][tid + cvec], gwr = g_s[buf][tid + cvec];
+                uint32_t cpr[CW], cwr[CW];
+                #pragma unroll
+                for (int i = 0; i < CW; i++) { cpr[i] = c_s[pbuf][i][tid + cvec]; cwr[i] = c_s[buf][i][tid + cvec]; }
+                float a00[VEC], a01[VEC], a10[VEC], a11[VEC];      // gradients of windows (j, ow), (j, ow + 1), (j + 1, ..)
+                Elem<T>::unpack(gp, a00);
+                Elem<T>::unpack(gpr, a01);
+                Elem<T>::unpack(gw, a10);
+                Elem<T>::unpack(gwr, a11);
+                float dz[4][VEC];
+                #pragma unroll
+                for (int e = 0; e < VEC; e++) {
+                    const int sh = 8 * (e % 4), q = e / 4;
+                    const uint32_t t00 = (cp[q] >> sh) & 15u, t01 = (cpr[q] >> sh) & 15u;
+                    const uint32_t t10 = (code[q] >> sh) & 15u, t11 = (cwr[q] >> sh) & 15u;
+                    // (row-major window order; an unmatched window adds zero)
+                    dz[0][e] = t00 == 4u ? a00[e] : 0.f;
+                    dz[1][e] = (t00 == 5u ? a00[e] : 0.f) + (t01 == 3u ? a01[e] : 0.f);
+                    dz[2][e] = (t00 == 7u ? a00[e] : 0.f) + (t10 == 1u ? a10[e] : 0.f);
+                    dz[3][e] = (t00 == 8u ? a00[e] : 0.f) + (t01 == 6u ? a01[e] : 0.f);
+                    dz[3][e] += t10 == 2u ? a10[e] : 0.f;
+                    dz[3][e] += t11 == 0u ? a11[e] : 0.f;
+                    dz[0][e] += 0.f;                               // (0 + -0 = 0, as a sum from zero)
+                }
+                #pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const int row = 2 * j + (i >> 1), col = 2 * ow + (i & 1);
+                    if (row < h && col < w) {
+                        float o[VEC];
+                        T *dst = dn + (int64_t)(row * w + col) * C;
+                        if (BN) {
+                            float f[VEC];
+                            Elem<T>::unpack(xp[i], f);
+                            #pragma unroll
+                            for (int e = 0; e < VEC; e++)
+                                o[e] = bn_lin(f[e] - kc[e], par[1][v * VEC + e], par[2][v * VEC + e]) > 0.f ? dz[i][e] : 0.f;
+                            const vec16 ov = Elem<T>::pack(o);
+                            stg16(dst, ov);
+                            Elem<T>::unpack(ov, o);
+                            #pragma unroll
+                            for (int e = 0; e < VEC; e++) {        // (xhat's rstd multiplies the finished sum)
+                                s1[e] += o[e];
+                                s2[e] = __builtin_fmaf(o[e], (f[e] - kc[e]) - par[3][v * VEC + e], s2[e]);
+                            }
+                        } else {
+                            stg16(dst, Elem<T>::pack(dz[i]));
+                        }
+                    }
                 }
             }
-            uint8_t *cp = &codes[orow][ow * C + v * VEC];
+            xp[0] = xa[1]; xp[1] = xa[2]; xp[2] = xb[1]; xp[3] = xb[2];
+            gp = gw;
             #pragma unroll
-            for (int i = 0; i < VEC; i++) cp[i] = (uint8_t)code[i];
+            for (int i = 0; i < CW; i++) cp[i] = code[i];
         }
-        __syncthreads();
-        // phase 2: input rows 2j, 2j + 1
-        for (int t = tid; t < 2 * w * cvec; t += kThreads) {
-            const int ir = t / (w * cvec), col = (t - ir * w * cvec) / cvec;
-            const int row = 2 * j + ir;
-            if (row >= h) continue;
-            float dz[VEC];
-            #pragma unroll
-            for (int i = 0; i < VEC; i++) dz[i] = 0.f;
-            const int oh_lo = j, oh_hi = ir ? j + 1 : j;
-            const int ow_lo = col >> 1, ow_hi = (col & 1) ? (col + 1) >> 1 : col >> 1;
-            // the (at most 2 x 2) covering windows' gradients and the BN input
-            // loaded first at clamped positions, then summed in row-major
-            // window order
-            const int64_t q = (n * h + row) * w + col;
-            vec16 gv[4], xv = zero16();
-            bool win[4];
-            #pragma unroll
-            for (int w4 = 0; w4 < 4; w4++) {
-                const int oh = oh_lo + (w4 >> 1), ow = ow_lo + (w4 & 1);
-                win[w4] = oh <= oh_hi && oh < ho && ow <= ow_hi && ow < wo;
-                const int ohc = oh < ho ? oh : ho - 1, owc = ow < wo ? ow : wo - 1;
-                gv[w4] = ldg16(gy + ((n * ho + ohc) * wo + owc) * p.g_ldc + cv * VEC);
-            }
-            if (BN) xv = ldg16(x + q * p.x_ldc + cv * VEC);
-            #pragma unroll
-            for (int w4 = 0; w4 < 4; w4++) {
-                if (!win[w4]) continue;
-                const int oh = oh_lo + (w4 >> 1), ow = ow_lo + (w4 & 1);
-                const uint32_t tap = (uint32_t)((row - (2 * oh - 1)) * 3 + (col - (2 * ow - 1)));
-                float g[VEC];
-                Elem<T>::unpack(gv[w4], g);
-                const uint8_t *cp = &codes[oh - j][ow * C + cv * VEC];
-                #pragma unroll
-                for (int i = 0; i < VEC; i++)
-                    if (cp[i] == tap) dz[i] += g[i];
-            }
-            float o[VEC];
-            if (BN) {
-                float f[VEC];
-                Elem<T>::unpack(xv, f);
-                #pragma unroll
-                for (int i = 0; i < VEC; i++) o[i] = bn_lin(f[i] - kc[i], k[i], b[i]) > 0.f ? dz[i] : 0.f;
-                const vec16 ov = Elem<T>::pack(o);
-                stg16(dy + q * C + cv * VEC, ov);
-                Elem<T>::unpack(ov, o);
-                #pragma unroll
-                for (int i = 0; i < VEC; i++) {
-                    s1[i] += o[i];
-                    s2[i] += o[i] * (((f[i] - kc[i]) - mu[i]) * rs[i]);
-                }
-            } else {
-                stg16(dy + q * C + cv * VEC, Elem<T>::pack(dz));
-            }
-        }
-        __syncthreads();
+        __syncthreads();                            // (the buffers' next writer is another chunk's first row)
     }
     if (BN) {
-        // threads tid = cv + cvec*u hold channel vector cv
+        // threads tid = v + cvec ow hold channel vector v
         #pragma unroll
-        for (int i = 0; i < VEC; i++) {
-            red[0][tid * VEC + i] = s1[i];
-            red[1][tid * VEC + i] = s2[i];
+        for (int e = 0; e < VEC; e++) {
+            const float rs = p.rstd[v * VEC + e];
+            red[0][tid * VEC + e] = act ? s1[e] : 0.f;
+            red[1][tid * VEC + e] = act ? s2[e] * rs : 0.f;
         }
         __syncthreads();
         if (tid < C) {
-            const int v = tid / VEC, i = tid - v * VEC;
-            float a = 0.f, bb = 0.f;
-            for (int u = v; u < kThreads; u += cvec) { a += red[0][u * VEC + i]; bb += red[1][u * VEC + i]; }
+            const int cv = tid / VEC, e = tid - cv * VEC;
+            float a = 0.f, b = 0.f;
+            for (int u = cv; u < wo * cvec; u += cvec) { a += red[0][u * VEC + e]; b += red[1][u * VEC + e]; }
             float *pr = p.part + (int64_t)blockIdx.x * 2 * C;
             pr[tid] = a;
-            pr[C + tid] = bb;
+            pr[C + tid] = b;
         }
     }
 }
@@ -1010,10 +1122,18 @@ hipError_t launch_maxpool_fwd(int dtype, const MaxPoolParams &p, bool bn, bool s
     return hipGetLastError();
 }
 
+// Row pairs per chunk: the fewest chunks of which every CU has two (a chunk
+// reduces one window row more than it owns), at most kMaxPoolBwdGroups
+// workgroups, one partial row each.
+static int maxpool_bwd_pairs(int n, int h)
+{
+    const int64_t hp = (h + 1) / 2, per = (int64_t)n * hp / 512;
+    return (int)(per < 1 ? 1 : (per < hp ? per : hp));
+}
 int64_t maxpool_bwd_groups(int n, int h)
 {
-    const int64_t items = (int64_t)n * ((h + 1) / 2);
-    return items < kMaxPoolBwdGroups ? (items < 1 ? 1 : items) : kMaxPoolBwdGroups;
+    const int64_t chunks = (int64_t)n * ceil_div((h + 1) / 2, maxpool_bwd_pairs(n, h));
+    return chunks < kMaxPoolBwdGroups ? (chunks < 1 ? 1 : chunks) : kMaxPoolBwdGroups;
 }
 
 hipError_t launch_maxpool_bwd(int dtype, const MaxPoolParams &p, bool bn, hipStream_t s)
@@ -1026,12 +1146,13 @@ hipError_t launch_maxpool_bwd(int dtype, const MaxPoolParams &p, bool bn, hipStr
     const unsigned g = (unsigned)maxpool_bwd_groups(p.n, p.h);
     const double e = dtype == DT_BF16 ? 2.0 : 4.0, m = (double)p.n * p.h * p.w;
     TraceScope tr(KC_SWEEP, KID_MAXPOOL, s, e * p.c * ((bn ? 2.0 : 1.0) * m + (double)p.n * p.ho * p.wo), 0.0);
+    const int pairs = maxpool_bwd_pairs(p.n, p.h), cpi = (int)ceil_div((p.h + 1) / 2, pairs);
+    const int64_t chunks = (int64_t)p.n * cpi;
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(g), dim3(mp_threads(vec)), 0, s, p, pairs, cpi, chunks); };
     if (dtype == DT_BF16) {
-        if (bn) hipLaunchKernelGGL((k_maxpool_bwd<bf16_t, true>), dim3(g), dim3(kThreads), 0, s, p);
-        else hipLaunchKernelGGL((k_maxpool_bwd<bf16_t, false>), dim3(g), dim3(kThreads), 0, s, p);
+        if (bn) go(k_maxpool_bwd<bf16_t, true>); else go(k_maxpool_bwd<bf16_t, false>);
     } else {
-        if (bn) hipLaunchKernelGGL((k_maxpool_bwd<float, true>), dim3(g), dim3(kThreads), 0, s, p);
-        else hipLaunchKernelGGL((k_maxpool_bwd<float, false>), dim3(g), dim3(kThreads), 0, s, p);
+        if (bn) go(k_maxpool_bwd<float, true>); else go(k_maxpool_bwd<float, false>);
     }
     return hipGetLastError();
 }
