@@ -287,6 +287,9 @@ __global__ __launch_bounds__(kThreads, 2) void k_stem_wgrad(StemParams p)
         #pragma unroll
         for (int cb = 0; cb < 4; cb++) acc[ki][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // (128 images of 224 x 224: 236 us with loads, transform, barrier and
+    // products in sequence, a division per staged pixel and position; 110 us
+    // with the next item's loads in flight during the products.)
     // Register stage of one item: image pixel slots q = tid + j 256 of the
     // kSIR x RPX staged pixels, gradient slots (pixel tid / 8 + 32 j, channel
     // vector tid % 8).  Their rows and columns are split once; an item is a
@@ -565,9 +568,11 @@ __global__ __launch_bounds__(kThreads) void k_maxpool_fwd(MaxPoolParams p, int64
 // all come from registers, except what the right-hand neighbour's windows
 // hold, which goes through LDS (three row buffers, one barrier per row).
 // A value wins over an earlier one only if it is greater (NaN never wins).
-// What bounds it: instructions (about 800 per row pair and wave) next to HBM;
-// 128 images of 112 x 112 x 64: 240 us with the windows of every row pair
-// scanned twice from global memory and their codes in LDS bytes.
+// What bounds it: instructions (about 1000 vector ones per row pair and wave)
+// and the load round trip of each row.  128 images of 112 x 112 x 64: 240 us
+// with the windows of every row pair scanned twice from global memory and
+// their codes in LDS bytes, 219 us this way (HBM floor 83); 1024 or 2048
+// chunks instead of 512: 228 and 252 us.
 constexpr int mp_threads(int vec) { return kMaxPoolMaxWo * kMaxPoolMaxC / vec; }
 template <typename T, bool BN>
 __global__ __launch_bounds__(mp_threads(Elem<T>::VEC), 4) void k_maxpool_bwd(MaxPoolParams p, int pairs_per_chunk,
@@ -620,17 +625,18 @@ __global__ __launch_bounds__(mp_threads(Elem<T>::VEC), 4) void k_maxpool_bwd(Max
         Elem<T>::unpack(vm, m_);
         Elem<T>::unpack(vr, r);
         cols = 0u;
+        // (a tap outside the image: sign(gamma) x - inf, which never wins)
+        const float ol = in && in_l ? 0.f : -INFINITY, om = in ? 0.f : -INFINITY, orr = in && in_r ? 0.f : -INFINITY;
         #pragma unroll
         for (int e = 0; e < VEC; e++) {
             const float sg = BN ? sgn[e] : 1.f;
-            float b = -INFINITY;
-            uint32_t c = 0u;
-            const float kl = in && in_l ? sg * l[e] : -INFINITY, km = in ? sg * m_[e] : -INFINITY;
-            const float kr = in && in_r ? sg * r[e] : -INFINITY;
-            if (kl > b) b = kl;
-            if (km > b) { b = km; c = 1u; }
-            if (kr > b) { b = kr; c = 2u; }
-            best[e] = b;
+            const float kl = __builtin_fmaf(sg, l[e], ol), km = __builtin_fmaf(sg, m_[e], om);
+            const float kr = __builtin_fmaf(sg, r[e], orr);
+            float b = __builtin_fmaxf(kl, -INFINITY);              // (NaN never wins)
+            uint32_t c = km > b ? 1u : 0u;
+            b = __builtin_fmaxf(b, km);
+            c = kr > b ? 2u : c;
+            best[e] = __builtin_fmaxf(b, kr);
             cols |= c << (4 * e);
         }
     };
@@ -676,11 +682,10 @@ __global__ __launch_bounds__(mp_threads(Elem<T>::VEC), 4) void k_maxpool_bwd(Max
             for (int i = 0; i < CW; i++) code[i] = 0u;
             #pragma unroll
             for (int e = 0; e < VEC; e++) {
-                float b = -INFINITY;
-                uint32_t t = 0u;
-                if (hb[e] > b) { b = hb[e]; t = (hc >> (4 * e)) & 3u; }
-                if (ba[e] > b) { b = ba[e]; t = 3u + ((ca >> (4 * e)) & 3u); }
-                if (bb[e] > b) t = 6u + ((cb >> (4 * e)) & 3u);
+                // (a row without a value above -inf holds column 0: tap 0, as a scan that nothing wins)
+                uint32_t t = (hc >> (4 * e)) & 3u;
+                if (ba[e] > hb[e]) t = 3u + ((ca >> (4 * e)) & 3u);
+                if (bb[e] > __builtin_fmaxf(hb[e], ba[e])) t = 6u + ((cb >> (4 * e)) & 3u);
                 code[e / 4] |= t << (8 * (e % 4));
                 hb[e] = bb[e];
             }

@@ -138,3 +138,58 @@ def test_conv3x3_nan_and_inf_stay_local(B):
     want[1, 3:6, 0:2] = float("inf")
     got = out.float().cpu()
     assert bool((got == want[..., None]).all())
+
+
+@pytest.mark.parametrize("bf16,n,h,w,c", [
+    (True, 1, 1, 1, 8),         # one pixel, one vector
+    (False, 1, 2, 3, 4),
+    (True, 2, 5, 128, 64),      # widest rows: every thread a window column
+    (False, 2, 4, 127, 64),     # the same with an odd last column, float32 vectors
+    (True, 60, 35, 9, 16),      # chunks of two row pairs
+    (False, 90, 35, 6, 8),      # chunks of three
+    (True, 115, 18, 5, 32),     # chunks of two, the last of an image one pair
+])
+def test_maxpool_bwd_chunks(B, bf16, n, h, w, c):
+    """Small whole numbers (many ties) and whole-number gradients: every sum is
+    exact, so the result equals the oracle's."""
+    rng = np.random.default_rng(5)
+    x = rng.integers(-3, 4, size=(n, h, w, c)).astype(np.float64)
+    ho, wo = (h - 1) // 2 + 1, (w - 1) // 2 + 1
+    gy = rng.integers(-8, 9, size=(n, ho, wo, c)).astype(np.float64)
+    xd, gd = dev(x, bf16), dev(gy, bf16)
+    dz = torch.full((n, h, w, c), 9.0, dtype=xd.dtype, device=xd.device)
+    B.bnr_maxpool_bn_bwd(xd, None, gd, dz, n, h, w)
+    torch.cuda.synchronize()
+    ref = P.maxpool_bwd(x, gy, 3, 2, 1)
+    np.testing.assert_array_equal(host(dz), ref)
+    # with a BN of unit scale and an offset that no input cancels, the mask is exact too
+    ones, zeros = torch.ones(c, device="cuda"), torch.zeros(c, device="cuda")
+    bn = B.BN(ones.clone(), torch.full((c,), 0.5, device="cuda"), 1e-5, zeros.clone(), ones.clone(), ones.clone())
+    dg, db = torch.empty(c, device="cuda"), torch.empty(c, device="cuda")
+    B.bnr_maxpool_bn_bwd(xd, bn, gd, dz, n, h, w, dg, db)
+    torch.cuda.synchronize()
+    refy = P.maxpool_bwd(P.relu_fwd(x + 0.5), gy, 3, 2, 1) * (x + 0.5 > 0)
+    np.testing.assert_array_equal(host(dz), refy)
+    np.testing.assert_allclose(host(db), refy.reshape(-1, c).sum(0), rtol=0, atol=1e-6 * np.abs(refy).sum() / c + 1e-6)
+    np.testing.assert_allclose(host(dg), (refy * x).reshape(-1, c).sum(0), rtol=0, atol=4e-6 * np.abs(refy).sum() / c + 1e-6)
+
+
+@pytest.mark.parametrize("n,h,w,c_in", [(1, 1, 1, 3), (3, 9, 255, 3), (2, 256, 256, 4), (700, 5, 6, 1)])
+def test_stem_wgrad_items(B, n, h, w, c_in):
+    """Weight gradient of the first CONV at the ends of its staging slots: one
+    output pixel, the widest image (all slots), an odd last row, more items
+    than workgroups.  Whole numbers: exact in bf16 and in float32 sums."""
+    rng = np.random.default_rng(6)
+    ho, wo = (h - 1) // 2 + 1, (w - 1) // 2 + 1
+    img = np.zeros((n, h, w, 4))
+    img[..., :c_in] = rng.integers(-2, 3, size=(n, h, w, c_in))
+    g = rng.integers(-2, 3, size=(n, ho, wo, 64)).astype(np.float64)
+    dw = torch.empty((7, 7, c_in, 64), dtype=torch.float32, device="cuda")
+    B.bnr_stem_wgrad(dev(img, True), c_in, B.grad_dense(dev(g, True)), dw)
+    torch.cuda.synchronize()
+    ip = np.pad(img[..., :c_in], ((0, 0), (3, 4), (3, 4), (0, 0)))
+    ref = np.empty((7, 7, c_in, 64))
+    for a in range(7):
+        for b in range(7):
+            ref[a, b] = ip[:, a:a + 2 * ho:2, b:b + 2 * wo:2].reshape(-1, c_in).T @ g.reshape(-1, 64)
+    np.testing.assert_array_equal(host(dw), ref)
