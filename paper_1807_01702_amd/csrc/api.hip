@@ -288,6 +288,13 @@ void fill_rows(RowsParams &rp, const bnr_conv_desc *d, int K, int N)
 bnr_status launch_conv_any(RowsParams &rp, const bnr_conv_desc *d, const void *w, int transpose, void *wpack,
                            int64_t *rows, hipStream_t s)
 {
+    if (conv_poolup_supported(rp)) {
+        rp.wraw = w;
+        rp.wtrans = transpose;
+        *rows = conv_poolup_partial_rows(rp.m, rp.N);
+        TRY_HIP(launch_conv_poolup(rp, s), "conv data gradient");
+        return BNR_OK;
+    }
     if (rp.taps == 1 && conv1x1_supported(rp.dtype, rp.K, rp.N, rp.epi)) {
         rp.wraw = w;
         rp.wtrans = transpose;

@@ -16,7 +16,7 @@
 // per workgroup for the float64 combine.
 //
 // Prologue / epilogue modes are those of conv_rows.hip (PRO_BNRELU, PRO_RELU,
-// PRO_BNGRAD, PRO_POOLUP; EPI_STORE, EPI_STATS, EPI_BNBWD, EPI_RELUMASK).
+// PRO_BNGRAD; EPI_STORE, EPI_STATS, EPI_BNBWD, EPI_RELUMASK).
 #include "common.hpp"
 #include "kernels.hpp"
 #include "mfma.hpp"
@@ -69,7 +69,7 @@ static P1Geom p1_geom(int K, int N, bool fine = false)
 // residual block's BN + identity + ReLU: a second operand, and the result is
 // stored as a side output), PC_BNRELU_SAVE (BN+ReLU whose result z is also
 // stored as a side output: the materialised O2' sweep), PC_RUNTIME (PRO_NONE /
-// PRO_BNRELU / PRO_RELU / PRO_POOLUP chosen at run time).
+// PRO_BNRELU / PRO_RELU chosen at run time).
 // The BN-backward epilogues read z instead of x when p.e_zsrc is set (see
 // the epilogue parameters below).
 enum { PC_RUNTIME = 0, PC_BNGRAD = 1, PC_BNRELU = 2, PC_BNRELU_POOL = 3, PC_BNADD = 4, PC_BNRELU_SAVE = 5 };
@@ -112,9 +112,8 @@ __global__ __launch_bounds__(kP1Threads) void k_conv1x1(RowsParams p, P1Geom g)
     const int H = p.h, W = p.w;
     const T *wsrc = reinterpret_cast<const T *>(p.wraw);
     const int a_ldc = (int)p.a_ldc, a2_ldc = (int)p.a2_ldc, y_ldc = (int)p.y_ldc, ex_ldc = (int)p.ex_ldc;
-    const bool pool = !POOLF && pro == PRO_POOLUP;
     // operand views as raw buffers (launcher guarantees each spans < 2^31 bytes)
-    const int64_t arows = pool ? (int64_t)m / 4 : (POOLF ? (int64_t)m * 4 : m);
+    const int64_t arows = POOLF ? (int64_t)m * 4 : m;
     const __amdgpu_buffer_rsrc_t abuf = buf_view(p.a, (uint32_t)(((arows - 1) * a_ldc + K) * 2));
     const __amdgpu_buffer_rsrc_t a2buf = buf_view(TWO ? p.a2 : p.a, TWO ? (uint32_t)(((int64_t)(m - 1) * a2_ldc + K) * 2) : 0u);
     const int side_ldc = (int)p.side_ldc;
@@ -253,17 +252,6 @@ __global__ __launch_bounds__(kP1Threads) void k_conv1x1(RowsParams p, P1Geom g)
                     ra[j * PF + f] = bld16(abuf, ok ? (uint32_t)(pp * a_ldc + c) * 2u : kBufOff);
                 }
             }
-        } else if (!BNG && pool) {      // (the deferred-gradient variants never read a pooled gradient)
-            #pragma unroll
-            for (int j = 0; j < NVA; j++) {
-                const int pp = p0 + sr[j], c = sc[j];
-                const bool ok = sv[j] && c < K && pp < lim;
-                const int img = pp / (H * W);
-                const int rem = pp - img * H * W;
-                const int y = rem / W, x = rem - y * W;
-                const int q = (img * (H / 2) + y / 2) * (W / 2) + x / 2;
-                ra[j] = bld16(abuf, ok ? (uint32_t)(q * a_ldc + c) * 2u : kBufOff);
-            }
         } else {
             #pragma unroll
             for (int j = 0; j < NVA; j++) {
@@ -346,15 +334,6 @@ __global__ __launch_bounds__(kP1Threads) void k_conv1x1(RowsParams p, P1Geom g)
                 Elem<T>::unpack(ra[j], f);
                 #pragma unroll
                 for (int e = 0; e < VEC; e++) f[e] = f[e] > 0.f ? f[e] : 0.f;
-                put(j, Elem<T>::pack(f));
-            }
-        } else if (!BNG && pool) {                        // PRO_POOLUP: g[p/2] / 4
-            #pragma unroll
-            for (int j = 0; j < NVA; j++) {
-                float f[VEC];
-                Elem<T>::unpack(ra[j], f);
-                #pragma unroll
-                for (int e = 0; e < VEC; e++) f[e] *= 0.25f;
                 put(j, Elem<T>::pack(f));
             }
         } else {
@@ -630,7 +609,6 @@ static hipError_t run_p1(const RowsParams &p, const P1Geom &g, hipStream_t s, in
     if (BNG) a *= 2.0;
     if (PC == PC_BNADD) a *= 3.0;                   // y and the identity read, the result written
     if (PC == PC_BNRELU_SAVE) a *= 2.0;             // x read, z written
-    if (p.pro == PRO_POOLUP) a /= 4.0;
     if (PC == PC_BNRELU_POOL) a *= 4.0;             // four input pixels per row
     double out = m * p.N;
     if (EK == EK_STORE_ACC || EK == EK_RELUMASK || EK == EK_BNBWD || EK == EK_BNBWD_SC) out += m * p.N;
@@ -710,7 +688,7 @@ hipError_t launch_conv1x1(const RowsParams &p, hipStream_t s, int64_t *rows)
     if ((p.epi == EPI_STATS || p.epi == EPI_BNBWD) && !p.part) return hipErrorInvalidValue;
     if (p.epi == EPI_BNBWD && (!p.ex || !p.e_mean || !p.e_rstd || !p.e_gamma || !p.e_beta)) return hipErrorInvalidValue;
     if (p.epi == EPI_RELUMASK && !p.ex) return hipErrorInvalidValue;
-    if (p.pro == PRO_POOLUP && (p.h % 2 || p.w % 2 || (int64_t)p.n * p.h * p.w != p.m)) return hipErrorInvalidValue;
+    if (p.pro == PRO_POOLUP) return hipErrorInvalidValue;        // conv_poolup.hip
     const bool poolf = p.pro == PRO_BNRELU_POOL;
     if (poolf && (p.h % 2 || p.w % 2 || (int64_t)p.n * p.h * p.w != 4 * p.m || p.wtrans ||
                   (p.epi != EPI_STORE && p.epi != EPI_STATS) || p.accumulate || !p.p_mean || !p.p_gamma ||

@@ -22,7 +22,8 @@
 //                staging loop, by the first column tile, the tile's own rows)
 //   PRO_BNGRAD : a = A dy + B x + C  (deferred BN input gradient from dy and
 //                the BN input x; coefficients by deferred_coef)
-//   PRO_POOLUP : a = g[n][y/2][x/2] / 4   (2x2 average-pooling gradient)
+//   PRO_POOLUP : a = g[n][y/2][x/2] / 4   (2x2 average-pooling gradient;
+//                bf16 1x1 data is conv_poolup.hip's)
 //   PRO_BNRELU_POOL: row = 2x2 window; a = mean over its four pixels of
 //                max(gamma*(x-mean)*rstd + beta, 0)  (1x1 only, general
 //                staging loop)
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(kThreads) void k_conv_rows(RowsParams p)
             // source pixel is fixed for the whole tile.
             constexpr int NA = (BM * VPR + kThreads - 1) / kThreads, NB = (BN * VPR + kThreads - 1) / kThreads;
             const int pro = SP == SP_FWD_BNRELU ? PRO_BNRELU : (SP == SP_DGRAD_BNGRAD ? PRO_BNGRAD : p.pro);
-            const bool pool = pro == PRO_POOLUP;
+            const bool pool = kF32 && pro == PRO_POOLUP;
             const int64_t src_rows = pool ? m / 4 : m;
             const __amdgpu_buffer_rsrc_t abuf = buf_view(p.a, (uint32_t)(((src_rows - 1) * p.a_ldc + K) * sizeof(T)));
             const __amdgpu_buffer_rsrc_t a2buf =

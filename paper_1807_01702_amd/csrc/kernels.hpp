@@ -159,6 +159,11 @@ hipError_t launch_conv3x3(const RowsParams &p, hipStream_t s);
 bool conv_f32_supported(const RowsParams &p);
 hipError_t launch_conv_f32(const RowsParams &p, hipStream_t s);
 
+// ---- bf16 1x1 data gradient through 2x2 average pooling (PRO_POOLUP), over window rows ----
+bool conv_poolup_supported(const RowsParams &p);
+int64_t conv_poolup_partial_rows(int64_t m, int N);    // statistics partial rows it writes (at most rows_mtiles)
+hipError_t launch_conv_poolup(const RowsParams &p, hipStream_t s);
+
 // ---- weight gradient -------------------------------------------------------
 enum { GB_DENSE = 0, GB_BNGRAD = 1, GB_POOLUP = 2 };
 struct WgradParams {

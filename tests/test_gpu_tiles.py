@@ -193,3 +193,65 @@ def test_stem_wgrad_items(B, n, h, w, c_in):
         for b in range(7):
             ref[a, b] = ip[:, a:a + 2 * ho:2, b:b + 2 * wo:2].reshape(-1, c_in).T @ g.reshape(-1, 64)
     np.testing.assert_array_equal(host(dw), ref)
+
+
+@pytest.mark.parametrize("n,h,w,ci,co", [
+    (1, 2, 2, 8, 8),            # one window, one vector
+    (1, 6, 10, 136, 72),        # a short window tile, two column tiles, two K chunks (the last of 8 channels)
+    (3, 14, 14, 264, 264),      # N and K past the persistent kernel, ragged
+    (8, 32, 32, 32, 64),        # whole 32-window tiles, one K chunk
+    (64, 46, 46, 256, 40),      # 64-window tiles, the last one short
+])
+def test_pooled_gradient_forms(B, n, h, w, ci, co):
+    """The 1x1 data gradient of a pooled gradient runs over windows: every form
+    of its epilogue equals the general kernels' on the gradient written out per
+    pixel (g / 4 is exact), within one rounding of the stored type."""
+    rtol, m = RTOL[True], n * h * w
+    x = dev(synth.normal(5, "x", (n, h, w, ci + 8), bf16=True), True)[..., :ci]
+    gp = dev(synth.normal(5, "g", (n, h // 2, w // 2, co + 8), bf16=True), True)[..., :co]
+    wd = dev(synth.conv_weight(5, "w", 1, ci, co, True), True)
+    up = (gp * 0.25).repeat_interleave(2, 1).repeat_interleave(2, 2).contiguous()
+    p1 = synth.bn_params(5, "bn1", ci)
+    gam = f32dev(p1["gamma"])
+    gam[ci // 2] = 0.0                                      # its vector reads x in the z form
+    bn = B.BN(gam, f32dev(p1["beta"]), 1e-5, x.reshape(-1, ci).float().mean(0).contiguous(),
+              torch.ones(ci, device="cuda"), torch.full((ci,), 1.25, device="cuda"))
+    z = torch.relu((x.float() - bn.mean) * bn.rstd * bn.gamma + bn.beta).to(torch.bfloat16).contiguous()
+    desc = B.desc_for(x, up, 1, n, h, w)
+
+    def run(src, form):
+        o = dict(dw=torch.empty(tuple(wd.shape), device="cuda"))
+        o.update({k: torch.full((ci,), 0.5, device="cuda") for k in ("dgamma", "dbeta", "alpha", "betap")})
+        y = torch.full((n, h, w, ci + 8), 3.0, dtype=x.dtype, device="cuda")
+        B.workspace(B.bnr_workspace_size(desc), x.device)
+        B._ws_cache[(x.device, 0)].fill_(255)
+        if form == "bn":
+            o["y"] = torch.empty((n, h, w, ci), dtype=x.dtype, device="cuda")
+            B.bnr_bwd_fused(desc, x, bn, wd, src, o["dw"], o["dgamma"], o["dbeta"], o["y"])
+        elif form == "z":
+            o["y"] = torch.empty((n, h, w, ci), dtype=x.dtype, device="cuda")
+            B.bnr_bwd_fused_o2(desc, x, bn, z, wd, src, o["dw"], o["dgamma"], o["dbeta"], o["y"])
+        elif form.startswith("split"):
+            B.bnr_bwd_fused_split(desc, x, bn, wd, src, o["dw"], o["dgamma"], o["dbeta"], y[..., :ci], o["alpha"],
+                                  o["betap"], accumulate=form == "split_acc")
+            o["y"] = y[..., :ci]
+        else:
+            B.bnr_bwd_fused(desc, x, None, wd, src, o["dw"], dx=y[..., :ci], dx_accumulate=form == "store_acc")
+            o["y"] = y[..., :ci]
+        torch.cuda.synchronize()
+        assert bool((y[..., ci:] == 3.0).all()), form + " wrote past its channels"
+        return o
+
+    for form in ("bn", "z", "split", "split_acc", "store", "store_acc"):
+        got, ref = run(B.grad_avgpool2(gp), form), run(B.grad_dense(up), form)
+        for k in ("y", "dw"):
+            assert_close(form + " " + k, host(got[k]), host(ref[k]), rtol)
+        if form in ("bn", "z"):                             # the sums are of the dy that was stored
+            d = host(got["y"]).reshape(m, ci)
+            xh = (host(x).reshape(m, ci) - host(bn.mean)) * host(bn.rstd)
+            assert np.all(np.abs(host(got["dbeta"]) - d.sum(0)) <= 1e-5 * np.abs(d).sum(0) + 1e-6)
+            if form == "bn":
+                assert np.all(np.abs(host(got["dgamma"]) - (d * xh).sum(0)) <= 1e-5 * np.abs(d * xh).sum(0) + 1e-6)
+        else:
+            for k in ("dgamma", "dbeta", "alpha", "betap"):
+                assert_close(form + " " + k, host(got[k]), host(ref[k]), rtol)
