@@ -225,7 +225,8 @@ def roofline(kernels, dtype, workload):
 # ---------------------------------------------------- HBM byte counters ----
 CSRC = os.path.join(ROOT, "paper_1807_01702_amd", "csrc")
 SHARED_SOURCES = ["common.hpp", "kernels.hpp", "mfma.hpp", "tiles.hpp"]
-CLASS_SOURCES = {"conv1x1": ["conv1x1.hip", "conv_rows.hip"], "conv3x3": ["conv3x3.hip", "conv_rows.hip"],
+CLASS_SOURCES = {"conv1x1": ["conv1x1.hip", "conv_poolup.hip", "conv_f32.hip", "conv_rows.hip"],
+                 "conv3x3": ["conv3x3.hip", "conv_f32.hip", "conv_rows.hip"],
                  "wgrad1x1": ["conv_wgrad.hip"], "wgrad3x3": ["conv_wgrad.hip"],
                  "stats_sweep": ["bn_kernels.hip"], "elementwise": ["bn_kernels.hip"],
                  "stats_combine": ["bn_kernels.hip"], "splitk_sum": ["bn_kernels.hip"], "pool": ["bn_kernels.hip"],
@@ -240,14 +241,16 @@ def kernel_class(name):
     if not m:
         return None
     k, targs = m.group(1), [t.strip() for t in (m.group(3) or "").split(",")]
-    if k == "k_conv1x1":
+    if k in ("k_conv1x1", "k_conv_poolup"):
         return "conv1x1"
+    if k == "k_conv_f32":
+        return "conv1x1" if targs[0] == "1" else "conv3x3"
     if k == "k_conv3x3":
         return "conv3x3"
     if k == "k_conv_rows":
         return "conv1x1" if len(targs) > 1 and targs[1] == "1" else "conv3x3"
-    if k in ("k_wgrad_tr", "k_wgrad"):
-        taps = targs[0] if k == "k_wgrad_tr" else (targs[1] if len(targs) > 1 else "")
+    if k in ("k_wgrad_tr", "k_wgrad_f32", "k_wgrad"):
+        taps = targs[0] if k != "k_wgrad" else (targs[1] if len(targs) > 1 else "")
         return "wgrad1x1" if taps == "1" else "wgrad3x3"
     return {"k_stats_partial": "stats_sweep", "k_elementwise": "elementwise", "k_addrelu_bwd": "elementwise",
             "k_stats_combine_one": "stats_combine", "k_stats_combine1": "stats_combine",

@@ -3,12 +3,12 @@
 //
 // A workgroup (four waves) computes BM pixels x 16 WN output channels; a wave
 // owns 16 of the channels and all (WN = 4) or half (WN = 2) of the pixels.
-//   * A: the pixel rows of a 32-channel chunk of K (plus a W + 1 row halo on
-//     each side for 3x3) are staged in LDS, transformed by the prologue, in
+//   * A: the pixel rows of a chunk of K (64 channels; 3x3: 16, plus a W + 1
+//     row halo on each side) are staged in LDS, transformed by the prologue, in
 //     two buffers: the next chunk is loaded to registers before the matrix-core
 //     work on the current one and written after it, one barrier per chunk.
 //   * Weights: read from the caller's array straight into matrix-core
-//     fragments, one step ahead (they stay in L2); no packing launch and no LDS.
+//     fragments, two or three steps ahead (they stay in L2); no packing launch and no LDS.
 //   * A 16x16x4 product takes one k per lane group; the groups take k = 4 q + s
 //     in step s = 0..3 of 16 consecutive k, so one 16-byte LDS read per 16
 //     pixels feeds four products.
@@ -398,7 +398,7 @@ template <int TAPS, int WN, int FP, int EK, bool WT>
 static hipError_t run_f32(const RowsParams &p, hipStream_t s)
 {
     const int arows = kF32BM + (TAPS == 9 ? 2 * (p.w + 1) : 0);
-    // statistics scratch: two arrays of 16 WM rows of 16 WN floats (2 KB at most)
+    // statistics scratch: two arrays of 16 WM rows of 16 WN floats (8 KB)
     const size_t lds = ((size_t)2 * arows * (f32_bk(TAPS) + 4) + 4 * (size_t)p.K) * sizeof(float);
     const double m = (double)p.m, e = 4.0;
     double a = m * p.K;
