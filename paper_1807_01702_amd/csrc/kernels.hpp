@@ -240,7 +240,7 @@ struct MaxPoolParams {
     const float *shift;           // forward statistics: sums of (y - shift) (NULL: 0)
 };
 int64_t maxpool_fwd_rows(int dtype, int64_t m_out, int c);
-int64_t maxpool_bwd_groups(int n, int h);
+int64_t maxpool_bwd_groups(int n, int h, int w, int c);
 hipError_t launch_maxpool_fwd(int dtype, const MaxPoolParams &p, bool bn, bool stats, hipStream_t s);
 hipError_t launch_maxpool_bwd(int dtype, const MaxPoolParams &p, bool bn, hipStream_t s);
 

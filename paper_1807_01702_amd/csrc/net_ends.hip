@@ -601,8 +601,8 @@ __global__ __launch_bounds__(mp_threads(Elem<T>::VEC), 4) void k_maxpool_bwd(Max
         par[3][tid] = BN ? p.mean[tid] : 0.f;
     }
     // no window past the last column, ever: code 15 matches no tap
-    for (int i = tid; i < 3 * CW * 16; i += NTHR) c_s[i / (CW * 16)][i / 16 % CW][(int)(wo * cvec) + i % 16] = 0x0f0f0f0fu;
-    for (int i = tid; i < 3 * 16; i += NTHR) g_s[i / 16][wo * cvec + i % 16] = zero16();
+    for (int i = tid; i < 3 * CW * 16; i += blockDim.x) c_s[i / (CW * 16)][i / 16 % CW][(int)(wo * cvec) + i % 16] = 0x0f0f0f0fu;
+    for (int i = tid; i < 3 * 16; i += blockDim.x) g_s[i / 16][wo * cvec + i % 16] = zero16();
     __syncthreads();
     const float *sgn = par[0] + v * VEC;
     float s1[VEC], s2[VEC], kc[VEC];
@@ -1127,17 +1127,32 @@ hipError_t launch_maxpool_fwd(int dtype, const MaxPoolParams &p, bool bn, bool s
     return hipGetLastError();
 }
 
-// Row pairs per chunk: the fewest chunks of which every CU has two (a chunk
-// reduces one window row more than it owns), at most kMaxPoolBwdGroups
-// workgroups, one partial row each.
-static int maxpool_bwd_pairs(int n, int h)
+// Threads of a workgroup: its window columns' vectors, in whole waves.
+static int mp_block(int wo, int cvec)
 {
-    const int64_t hp = (h + 1) / 2, per = (int64_t)n * hp / 512;
-    return (int)(per < 1 ? 1 : (per < hp ? per : hp));
+    const int t = (int)ceil_div((int64_t)wo * cvec, 64) * 64;
+    return t < 64 ? 64 : t;
 }
-int64_t maxpool_bwd_groups(int n, int h)
+
+// Row pairs per chunk: the fewest of which all chunks fit the chip at once (a
+// chunk reduces one window row more than it owns, so fewer and longer chunks
+// do less, but a few chunks past the last free place cost a whole round: 40
+// images of 112 x 112 took 86 us in 560 chunks for 512 places, 64 in 480; 60
+// of 50 x 50, 46 us with 512 threads, 32 with 256 and twice the chunks).  Places:
+// 1024 threads (128 registers each) and four workgroups' LDS per CU; counted
+// for 8 channels a thread (float32 data takes two rounds).
+static int maxpool_bwd_pairs(int n, int h, int w, int c)
 {
-    const int64_t chunks = (int64_t)n * ceil_div((h + 1) / 2, maxpool_bwd_pairs(n, h));
+    const int64_t hp = (h + 1) / 2;
+    int per_cu = 1024 / mp_block((w - 1) / 2 + 1, c / 8);
+    per_cu = per_cu < 1 ? 1 : (per_cu > 4 ? 4 : per_cu);
+    const int64_t cpi = 256 * per_cu / n;                   // chunks per image
+    return (int)(cpi < 1 ? hp : ceil_div(hp, cpi < hp ? cpi : hp));
+}
+// workgroups, one partial row each
+int64_t maxpool_bwd_groups(int n, int h, int w, int c)
+{
+    const int64_t chunks = (int64_t)n * ceil_div((h + 1) / 2, maxpool_bwd_pairs(n, h, w, c));
     return chunks < kMaxPoolBwdGroups ? (chunks < 1 ? 1 : chunks) : kMaxPoolBwdGroups;
 }
 
@@ -1148,12 +1163,12 @@ hipError_t launch_maxpool_bwd(int dtype, const MaxPoolParams &p, bool bn, hipStr
         p.c > kMaxPoolMaxC || p.wo > kMaxPoolMaxWo || cvec < 1 || (kThreads % cvec) ||
         p.ho != (p.h - 1) / 2 + 1 || p.wo != (p.w - 1) / 2 + 1)
         return hipErrorInvalidValue;
-    const unsigned g = (unsigned)maxpool_bwd_groups(p.n, p.h);
+    const unsigned g = (unsigned)maxpool_bwd_groups(p.n, p.h, p.w, p.c);
     const double e = dtype == DT_BF16 ? 2.0 : 4.0, m = (double)p.n * p.h * p.w;
     TraceScope tr(KC_SWEEP, KID_MAXPOOL, s, e * p.c * ((bn ? 2.0 : 1.0) * m + (double)p.n * p.ho * p.wo), 0.0);
-    const int pairs = maxpool_bwd_pairs(p.n, p.h), cpi = (int)ceil_div((p.h + 1) / 2, pairs);
+    const int pairs = maxpool_bwd_pairs(p.n, p.h, p.w, p.c), cpi = (int)ceil_div((p.h + 1) / 2, pairs);
     const int64_t chunks = (int64_t)p.n * cpi;
-    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(g), dim3(mp_threads(vec)), 0, s, p, pairs, cpi, chunks); };
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(g), dim3((unsigned)mp_block(p.wo, cvec)), 0, s, p, pairs, cpi, chunks); };
     if (dtype == DT_BF16) {
         if (bn) go(k_maxpool_bwd<bf16_t, true>); else go(k_maxpool_bwd<bf16_t, false>);
     } else {

@@ -146,7 +146,9 @@ def test_conv3x3_nan_and_inf_stay_local(B):
     (True, 2, 5, 128, 64),      # widest rows: every thread a window column
     (False, 2, 4, 127, 64),     # the same with an odd last column, float32 vectors
     (True, 60, 35, 9, 16),      # chunks of two row pairs
-    (False, 90, 35, 6, 8),      # chunks of three
+    (False, 150, 35, 6, 8),     # chunks of three
+    (True, 1100, 5, 4, 8),      # more images than places: whole images as chunks
+    (True, 33, 6, 66, 64),      # workgroups of five waves
     (True, 115, 18, 5, 32),     # chunks of two, the last of an image one pair
 ])
 def test_maxpool_bwd_chunks(B, bf16, n, h, w, c):
