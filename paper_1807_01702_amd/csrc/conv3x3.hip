@@ -554,9 +554,10 @@ __global__ __launch_bounds__(kP3Threads) void k_conv3x3(RowsParams p, P3Geom g)
     auto epi_tile = [&](int t, Epi &ep) __attribute__((always_inline)) {
         const float *rd = red + ((t - 1) & 1) * (WK * TR * ldr) + (ALT ? r0 % TR : r0) * ldr + n;
         vec16 vo[RPT];
-        float eM[VEC], eC0[VEC], eC1[VEC];
+        float eM[VEC], eR[VEC], eC0[VEC], eC1[VEC];
         if (BNB) {
             lds_f8(epi + n, eM);
+            lds_f8(epi + NPC + n, eR);
             lds_f8(epi + 2 * NPC + n, eC0);
             lds_f8(epi + 3 * NPC + n, eC1);
         }
@@ -608,7 +609,10 @@ __global__ __launch_bounds__(kP3Threads) void k_conv3x3(RowsParams p, P3Geom g)
                 #pragma unroll
                 for (int e = 0; e < VEC; e++) f[e] = yv[e] > 0.f ? f[e] : 0.f;
                 vo[j] = Elem<T>::pack(f);
-            } else if (BNB) {                 // (xhat's rstd multiplies the finished sum)
+            } else if (BNB) {
+                // (xhat per element, as in the other CONV kernels: rstd times the
+                // finished sum instead saved 0.3% and put dgamma up to 6%
+                // further from float64)
                 float x[VEC];
                 vec16 cm = cv;
                 const uint32_t keep = ok ? 0xffffffffu : 0u;
@@ -618,10 +622,11 @@ __global__ __launch_bounds__(kP3Threads) void k_conv3x3(RowsParams p, P3Geom g)
                 Elem<T>::unpack(ep.x[j < NVX ? j : 0], x);
                 #pragma unroll
                 for (int e = 0; e < VEC; e++) {
+                    const float xh = (x[e] - eM[e]) * eR[e];
                     const float d = bn_lin(x[e], eC0[e], eC1[e]) > 0.f ? f[e] : 0.f;
                     f[e] = d;
                     s1[e] += d;
-                    s2[e] = __builtin_fmaf(d, x[e] - eM[e], s2[e]);
+                    s2[e] += d * xh;
                 }
                 vo[j] = Elem<T>::pack(f);
             }
@@ -658,12 +663,10 @@ __global__ __launch_bounds__(kP3Threads) void k_conv3x3(RowsParams p, P3Geom g)
 
     // ---- per-workgroup statistics partial row ----
     if (EK == EK_STATS || BNB) {
-        float eR[VEC];
-        if (BNB) lds_f8(epi + NPC + n, eR);
         #pragma unroll
         for (int e = 0; e < VEC; e++) {
             red[r0 * NPC + n + e] = s1[e];
-            red[(RSTEP + r0) * NPC + n + e] = BNB ? s2[e] * eR[e] : s2[e];
+            red[(RSTEP + r0) * NPC + n + e] = s2[e];
         }
         lds_colsum2(red, RSTEP, NPC, NPC, kP3Threads, tid, p.part + (int64_t)blockIdx.x * 2 * N,
                     p.part + (int64_t)blockIdx.x * 2 * N + N, N);
