@@ -360,6 +360,7 @@ __global__ __launch_bounds__(kP3Threads) void k_conv3x3(RowsParams p, P3Geom g)
     }
     const char *zsrc_base = reinterpret_cast<const char *>(zs ? p.ex : (p.ex2 ? p.ex2 : p.ex));
     const int zsrc_ldc = zs ? ex_ldc : ex2_ldc;
+    const uint32_t zsrc_off0 = col_ok ? (uint32_t)n * ES : 0u;
 
     // ---- prologue transform of batch b, then the ring writes (slot0: its ring
     // slot, a multiple of TR).  The mode switch is wave-uniform and outside the
@@ -469,8 +470,9 @@ __global__ __launch_bounds__(kP3Threads) void k_conv3x3(RowsParams p, P3Geom g)
             ep.yoff[j] = ok ? ew[j].off[0] : kBufOff;
             if (EK == EK_STORE_ACC) ep.x[j < NVX ? j : 0] = bld16(ybuf, ep.yoff[j]);
             else if (ZK)       // z, or x (gamma = 0 in the vector): one load from this thread's
-                // source at a clamped pixel (a padding or past-the-end row is not used)
-                ep.x[j < NVX ? j : 0] = ldg16(zsrc_base + (ok ? ew[j].off[NOE - 1] : 0u));
+                // source; a row that is not stored reads the thread's own channels of
+                // pixel 0, because 0 times what it reads is added to their sums
+                ep.x[j < NVX ? j : 0] = ldg16(zsrc_base + (ok ? ew[j].off[NOE - 1] : zsrc_off0));
             else if (XOP) ep.x[j < NVX ? j : 0] = bld16(xbuf, ok ? ew[j].off[NOE - 1] : kBufOff);
             p3_step(ew[j], g.epi_adv, g, W, eld);
         }

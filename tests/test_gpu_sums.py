@@ -39,3 +39,33 @@ def test_dgamma_of_one_pixel_is_dy_times_xhat(B, k, ci, co):
     assert np.count_nonzero(d) > ci // 8
     np.testing.assert_array_equal(f32(dbeta), d)
     np.testing.assert_array_equal(f32(dgamma), d * ((xv - f32(bn.mean)) * f32(bn.rstd)))
+
+
+@pytest.mark.parametrize("n,h,w,ci,co", [(2, 5, 5, 64, 32), (1, 3, 7, 32, 24), (3, 9, 4, 128, 32)])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("src", ["z", "x"])
+def test_stored_z_backward_keeps_a_channels_infinity_to_itself(B, n, h, w, ci, co, value, src):
+    """The 3x3 data gradient on the stored z reads something for the rows of
+    its padded grid that are no pixel, and adds 0 times it: an infinite or NaN
+    value of channel 0 may reach dgamma of channel 0 only (src x: the vectors
+    that hold a gamma = 0 channel read x instead)."""
+    x = dev(synth.normal(4, "x", (n, h, w, ci), bf16=True), True)
+    g = dev(synth.normal(4, "g", (n, h, w, co), bf16=True), True)
+    wt = dev(synth.conv_weight(4, "w", 3, ci, co, True), True)
+    p = synth.bn_params(4, "bn", ci)
+    gam = f32dev(p["gamma"])
+    if src == "x":
+        gam[1::8] = 0.0
+    bn = B.BN(gam, f32dev(p["beta"]), 1e-5, torch.zeros(ci, device="cuda"), torch.ones(ci, device="cuda"),
+              torch.ones(ci, device="cuda"))
+    z = torch.relu(x.float() * gam + bn.beta).to(torch.bfloat16)
+    out = []
+    for v in (1.0, value):
+        (z if src == "z" else x)[0, 0, 0, 0] = v
+        dw = torch.empty((3, 3, ci, co), device="cuda")
+        dg, db = torch.empty(ci, device="cuda"), torch.empty(ci, device="cuda")
+        B.bnr_bwd_fused_o2(B.desc_for(x, g, 3, n, h, w), x, bn, z, wt, B.grad_dense(g), dw, dg, db, torch.empty_like(x))
+        torch.cuda.synchronize()
+        out.append((f32(dg), f32(db)))
+    for clean, got in zip(*out):
+        np.testing.assert_array_equal(got[1:], clean[1:])
