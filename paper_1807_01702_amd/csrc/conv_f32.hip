@@ -355,7 +355,8 @@ __global__ __launch_bounds__(kThreads, f32_waves(TAPS, WN, FP, WT)) void k_conv_
                 s1[e] += d;
                 s2[e] += d * d;
             } else if (BNB) {
-                const float xc = x[e] - kc[e], xh = (xc - mu[e]) * rs[e];
+                // (a row past the tensor adds zeros, whatever it was read from)
+                const float xc = x[e] - kc[e], xh = ok ? (xc - mu[e]) * rs[e] : 0.f;
                 const float d = ok && bn_lin(xc, c0[e], c1[e]) > 0.f ? f[e] : 0.f;
                 s1[e] += d;
                 s2[e] += d * xh;

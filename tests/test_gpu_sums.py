@@ -69,3 +69,26 @@ def test_stored_z_backward_keeps_a_channels_infinity_to_itself(B, n, h, w, ci, c
         out.append((f32(dg), f32(db)))
     for clean, got in zip(*out):
         np.testing.assert_array_equal(got[1:], clean[1:])
+
+
+@pytest.mark.parametrize("k,n,h,w,ci,co", [(1, 1, 5, 7, 8, 12), (1, 3, 9, 11, 40, 68), (3, 2, 6, 7, 20, 36)])
+def test_stored_z_backward_float32_rows_past_the_tensor(B, k, n, h, w, ci, co):
+    """The last tile's rows past the tensor add nothing: an infinite z of the
+    first pixel makes its channel's dgamma infinite (that pixel's own term),
+    not NaN, and touches no other channel."""
+    x, g = dev(synth.normal(4, "x", (n, h, w, ci)), False), dev(synth.normal(4, "g", (n, h, w, co)), False)
+    wt = dev(synth.conv_weight(4, "w", k, ci, co, False), False)
+    p = synth.bn_params(4, "bn", ci)
+    bn = B.BN(f32dev(p["gamma"]), f32dev(p["beta"]), 1e-5, torch.zeros(ci, device="cuda"),
+              torch.ones(ci, device="cuda"), torch.ones(ci, device="cuda"))
+    z = torch.relu(x * bn.gamma + bn.beta)
+    out = []
+    for v in (1.0, float("inf")):
+        z[0, 0, 0, 0] = v
+        dw = torch.empty((k, k, ci, co), device="cuda")
+        dg, db = torch.empty(ci, device="cuda"), torch.empty(ci, device="cuda")
+        B.bnr_bwd_fused_o2(B.desc_for(x, g, k, n, h, w), x, bn, z, wt, B.grad_dense(g), dw, dg, db, torch.empty_like(x))
+        torch.cuda.synchronize()
+        out.append(f32(dg))
+    assert np.isinf(out[1][0]), out[1][0]
+    np.testing.assert_array_equal(out[1][1:], out[0][1:])
