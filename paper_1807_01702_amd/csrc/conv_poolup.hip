@@ -221,6 +221,9 @@ __global__ __launch_bounds__(kThreads, BM == 64 && EK == EK_BNBWD_SCACC ? 2 : 3)
             dst[q] = reinterpret_cast<T *>(p.y) + (pix[j] + (q >> 1) * W + (q & 1)) * p.y_ldc + n;
             if (ACC) ov[q] = ldg16(dst[q]);
         }
+        // (a window's four pixels are added first, then the windows, and the
+        // threads' sums in pairs: chains rounded dgamma up to 20% further off)
+        float t1[8], t2[8];
         #pragma unroll
         for (int q = 0; q < 4; q++) {
             float o[8], old[8];
@@ -232,8 +235,8 @@ __global__ __launch_bounds__(kThreads, BM == 64 && EK == EK_BNBWD_SCACC ? 2 : 3)
                 for (int e = 0; e < 8; e++) {
                     const float xh = (x[e] - emu[e]) * ers[e];
                     const float d = bn_lin(x[e], eg[e], eb[e]) > 0.f ? f[e] : 0.f;
-                    s1[e] += d;
-                    s2[e] += d * xh;
+                    t1[e] = q ? t1[e] + d : d;
+                    t2[e] = q ? __builtin_fmaf(d, xh, t2[e]) : d * xh;
                     o[e] = EK == EK_BNBWD ? d : (ACC ? __builtin_fmaf(d, es[e], old[e]) : d * es[e]);
                 }
                 stg16(dst[q], Elem<T>::pack(o));
@@ -245,6 +248,9 @@ __global__ __launch_bounds__(kThreads, BM == 64 && EK == EK_BNBWD_SCACC ? 2 : 3)
                 stg16(dst[q], cv);
             }
         }
+        if (BNB)
+            #pragma unroll
+            for (int e = 0; e < 8; e++) { s1[e] += t1[e]; s2[e] += t2[e]; }
     }
     if (BNB) {
         __syncthreads();
@@ -254,8 +260,18 @@ __global__ __launch_bounds__(kThreads, BM == 64 && EK == EK_BNBWD_SCACC ? 2 : 3)
             red[r0 * kPuBN + v * 8 + e] = s1[e];
             red[(kPuRStep + r0) * kPuBN + v * 8 + e] = s2[e];
         }
-        lds_colsum2(red, kPuRStep, kPuBN, kPuBN, kThreads, tid, p.part + (int64_t)mt * 2 * N + n0,
-                    p.part + (int64_t)mt * 2 * N + N + n0, N - n0);
+        __syncthreads();
+        // one column a thread, its rows added in pairs
+        static_assert(kThreads == 2 * kPuBN && kPuRStep == 16, "columns of both sums, rows");
+        const int c = tid % kPuBN, k = tid / kPuBN;
+        float t[kPuRStep];
+        #pragma unroll
+        for (int j = 0; j < kPuRStep; j++) t[j] = red[(k * kPuRStep + j) * kPuBN + c];
+        #pragma unroll
+        for (int st = 1; st < kPuRStep; st *= 2)
+            #pragma unroll
+            for (int j = 0; j < kPuRStep; j += 2 * st) t[j] += t[j + st];
+        if (n0 + c < N) p.part[((int64_t)mt * 2 + k) * N + n0 + c] = t[0];
     }
 }
 

@@ -92,3 +92,36 @@ def test_stored_z_backward_float32_rows_past_the_tensor(B, k, n, h, w, ci, co):
         out.append(f32(dg))
     assert np.isinf(out[1][0]), out[1][0]
     np.testing.assert_array_equal(out[1][1:], out[0][1:])
+
+
+def _sum_errors(dgamma, dbeta, dy, x, bn):
+    """2-norm over the channels of the errors of both sums against float64 sums
+    of the stored dy, over the 2-norm of the sums of their terms' magnitudes."""
+    c = x.shape[-1]
+    d = dy.reshape(-1, c).double()
+    t = d * ((x.reshape(-1, c).double() - bn.mean.double()) * bn.rstd.double())
+    return (float((dgamma.double() - t.sum(0)).norm() / t.abs().sum(0).norm()),
+            float((dbeta.double() - d.sum(0)).norm() / d.abs().sum(0).norm()))
+
+
+def _bn_of(B, x, seed):
+    c = x.shape[-1]
+    p, xd = synth.bn_params(seed, "bn", c), x.reshape(-1, c).double()
+    mean = xd.mean(0)
+    var = (xd - mean).square().mean(0)
+    return B.BN(f32dev(p["gamma"]), f32dev(p["beta"]), 1e-5, mean.float(), var.float(), torch.rsqrt(var + 1e-5).float())
+
+
+def test_pooled_gradient_sums_round_no_further(B):
+    """dgamma of a pooled gradient, error over the sum of its terms' magnitudes
+    (512 channels): 1.53e-9 (a window's pixels, then pairs of threads); the
+    general kernels, pixel by pixel, have 1.58e-9, sums in chains 1.85e-9."""
+    n, h, w, ci, co = 32, 28, 28, 512, 256
+    x = dev(synth.normal(6, "x", (n, h, w, ci), bf16=True), True)
+    g = dev(synth.normal(6, "g", (n, h // 2, w // 2, co), bf16=True), True)
+    wt = dev(synth.conv_weight(6, "w", 1, ci, co, True), True)
+    bn = _bn_of(B, x, 6)
+    dy, dg, db = torch.empty_like(x), torch.empty(ci, device="cuda"), torch.empty(ci, device="cuda")
+    B.bnr_bwd_data(B.conv_desc(n, h, w, ci, co, 1, ci, co, B.dtype_code(x)), x, bn, wt, B.grad_avgpool2(g), dg, db, dy)
+    e = _sum_errors(dg, db, dy, x, bn)
+    assert e[0] <= 1.65e-9 and e[1] <= 5.2e-10, e
