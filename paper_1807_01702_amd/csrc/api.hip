@@ -1324,7 +1324,8 @@ size_t pool_ws(int n, int h, int w, int c)
     const int64_t m_out = (int64_t)n * ((h - 1) / 2 + 1) * ((w - 1) / 2 + 1);
     int64_t R = maxpool_fwd_rows(DT_BF16, m_out, c);
     if (maxpool_fwd_rows(DT_F32, m_out, c) > R) R = maxpool_fwd_rows(DT_F32, m_out, c);
-    if (maxpool_bwd_groups(n, h, w, c) > R) R = maxpool_bwd_groups(n, h, w, c);
+    for (const int dt : {DT_BF16, DT_F32})
+        if (maxpool_bwd_groups(dt, n, h, w, c) > R) R = maxpool_bwd_groups(dt, n, h, w, c);
     return align_up((size_t)R * 2 * c * 4) + align_up(stats_red_bytes(c));
 }
 
@@ -1557,7 +1558,7 @@ bnr_status bnr_maxpool_bn_bwd(int32_t n, int32_t h, int32_t w, int32_t c, bnr_dt
     TRY_HIP(launch_maxpool_bwd(dt_of(dtype), p, x_bn != nullptr, st), "max-pooling backward");
     if (x_bn) {
         const size_t red_off = pool_ws(n, h, w, c) - align_up(stats_red_bytes(c));
-        TRY_HIP(launch_stats_finalize(p.part, maxpool_bwd_groups(n, h, w, c), c, m, FIN_BWD, 0.f, nullptr, nullptr, nullptr,
+        TRY_HIP(launch_stats_finalize(p.part, maxpool_bwd_groups(dt_of(dtype), n, h, w, c), c, m, FIN_BWD, 0.f, nullptr, nullptr, nullptr,
                                       dbeta, dgamma, (char *)ws + red_off, st),
                 "backward sums combine");
     }

@@ -77,6 +77,7 @@ __device__ __forceinline__ vec16 zero16() { vec16 v; v.u[0] = v.u[1] = v.u[2] = 
 // neither a branch nor a zero-initialised destination (which would force the
 // compiler to wait for older memory operations before issuing them).
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 constexpr uint32_t kBufOff = 0x80000000u;       // an offset that is always out of range
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_view(const void *base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes, 0x00020000);

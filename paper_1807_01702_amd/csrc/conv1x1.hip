@@ -533,7 +533,7 @@ __global__ __launch_bounds__(kP1Threads) void k_conv1x1(RowsParams p, P1Geom g)
 }
 
 // ------------------------------------------------------------- launchers ---
-static int device_cus()
+int device_cus()
 {
     static int cus = 0;
     if (!cus) {

@@ -676,18 +676,6 @@ __global__ __launch_bounds__(kP3Threads) void k_conv3x3(RowsParams p, P3Geom g)
 }
 
 // ------------------------------------------------------------- launchers ---
-static int p3_cus()
-{
-    static int cus = 0;
-    if (!cus) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-            cus = 256;
-    }
-    return cus;
-}
-
 bool conv3x3_supported(int dtype, int K, int N, int H, int W)
 {
     if (dtype != DT_BF16 || K > 128 || N > 128 || W > kP3MaxW || W < 1 || H > kP3MaxH || H < 1) return false;
@@ -704,7 +692,7 @@ bool conv3x3_supported(int dtype, int K, int N, int H, int W)
 int64_t conv3x3_partial_rows(int64_t m)
 {
     const int64_t tiles = ceil_div(m, 32);
-    const int64_t g = p3_cus();
+    const int64_t g = device_cus();
     return tiles < g ? tiles : g;
 }
 

@@ -145,6 +145,8 @@ hipError_t launch_pack_weights(int dtype, const void *w, int k, int c_in, int c_
                                hipStream_t s);
 hipError_t launch_conv_rows(const RowsParams &p, hipStream_t s);
 
+int device_cus();             // compute units of the current device (256 without one)
+
 // ---- persistent 1x1 CONV (weights resident in LDS, one workgroup per CU) ----
 bool conv1x1_supported(int dtype, int K, int N, int epi);
 int64_t conv1x1_partial_rows(int64_t m);      // upper bound of the statistics partial rows it writes
@@ -240,7 +242,7 @@ struct MaxPoolParams {
     const float *shift;           // forward statistics: sums of (y - shift) (NULL: 0)
 };
 int64_t maxpool_fwd_rows(int dtype, int64_t m_out, int c);
-int64_t maxpool_bwd_groups(int n, int h, int w, int c);
+int64_t maxpool_bwd_groups(int dtype, int n, int h, int w, int c);       // partial rows
 hipError_t launch_maxpool_fwd(int dtype, const MaxPoolParams &p, bool bn, bool stats, hipStream_t s);
 hipError_t launch_maxpool_bwd(int dtype, const MaxPoolParams &p, bool bn, hipStream_t s);
 

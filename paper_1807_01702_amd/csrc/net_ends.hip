@@ -559,222 +559,321 @@ __global__ __launch_bounds__(kThreads) void k_maxpool_fwd(MaxPoolParams p, int64
 // is.  With BN that is the gradient of the ReLU output: dy = dz [y > 0] (y
 // recomputed from x) is stored and the BN reductions sum(dy), sum(dy * xhat) of
 // the stored dy are accumulated; without BN dz is stored.
-// A workgroup takes chunks of consecutive row pairs of
-// one image; thread (ow, v) owns channel vector v of window column ow and of
-// the input columns 2 ow, 2 ow + 1.  Per window row it reads two input rows
-// (the third is carried: every input row is reduced over its three columns
-// once, "first maximum" kept as value and column), so the first-maximum tap of
-// every window, the gradients routed to a pixel block and the block's BN input
-// all come from registers, except what the right-hand neighbour's windows
-// hold, which goes through LDS (three row buffers, one barrier per row).
+// A workgroup takes chunks of consecutive row pairs of one image; thread
+// (ow, v) owns four channels v of window column ow and of the input columns
+// 2 ow, 2 ow + 1.  Per window row it reads two input rows (the third is
+// carried: every input row is reduced over its three columns once, "first
+// maximum" kept as value and column), so the first-maximum tap of every window,
+// the gradients routed to a pixel and the pixel's BN input all come from
+// registers, except what the right-hand neighbour's windows hold, which goes
+// through LDS (three row buffers, one barrier per row).  Window row oh finishes
+// input row 2 oh - 1 (which it shares with window row oh - 1) and input row
+// 2 oh (its own).  The sums add the two pixels of an input row first and the
+// workgroup's columns in float64.
 // A value wins over an earlier one only if it is greater (NaN never wins).
-// What bounds it: instructions (about 1000 vector ones per row pair and wave)
-// and the load round trip of each row.  128 images of 112 x 112 x 64: 240 us
-// with the windows of every row pair scanned twice from global memory and
-// their codes in LDS bytes, 219 us this way (HBM floor 83); 1024 or 2048
-// chunks instead of 512: 228 and 252 us.
-constexpr int mp_threads(int vec) { return kMaxPoolMaxWo * kMaxPoolMaxC / vec; }
-template <typename T, bool BN>
-__global__ __launch_bounds__(mp_threads(Elem<T>::VEC), 4) void k_maxpool_bwd(MaxPoolParams p, int pairs_per_chunk,
-                                                                            int chunks_per_image, int64_t chunks)
+// What bounds it: instruction issue and the load round trip of each row; rows
+// are addressed by a scalar base and a 32-bit offset a column.  128 images of
+// 112 x 112 x 64 in bf16: 249 us with the windows of every row pair scanned
+// twice from global memory, 137 us this way (HBM floor 83); 5 of 17 x 17: 11.9
+// and 10.1.  Eight bf16 channels a thread spilled registers (215 us; 13.1);
+// without spilling they are no faster on large inputs and slower on small ones,
+// which are one chain of steps (16 of 65 x 65: 27.8 us against 18.9).
+constexpr int kMpVec = 4;                            // channels of a thread
+constexpr int kMpThreads = kMaxPoolMaxWo * kMaxPoolMaxC / kMpVec;
+// the channels of one 32-bit word
+template <typename T> struct MpWord;
+template <> struct MpWord<float> {
+    static constexpr int N = 1;
+    __device__ static __forceinline__ void unpack(uint32_t w, float *f) { f[0] = __uint_as_float(w); }
+    __device__ static __forceinline__ uint32_t pack(const float *f) { return __float_as_uint(f[0]); }
+};
+template <> struct MpWord<bf16_t> {
+    static constexpr int N = 2;
+    __device__ static __forceinline__ void unpack(uint32_t w, float *f) {
+        f[0] = __uint_as_float(w << 16);
+        f[1] = __uint_as_float(w & 0xffff0000u);
+    }
+    __device__ static __forceinline__ uint32_t pack(const float *f) { return pack2bf(f[0], f[1]); }
+};
+// a thread's vector of NW words
+template <int NW> struct alignas(4 * NW) MpVec {
+    uint32_t u[NW];
+    __device__ static __forceinline__ MpVec load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+        if constexpr (NW == 4) return __builtin_bit_cast(MpVec, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+        else return __builtin_bit_cast(MpVec, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    }
+    __device__ __forceinline__ void store(__amdgpu_buffer_rsrc_t r, uint32_t off) const {
+        if constexpr (NW == 4) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, *this), r, off, 0, 0);
+        else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, *this), r, off, 0, 0);
+    }
+};
+// LDS of a workgroup of nthr threads: three row buffers of the windows'
+// gradients and codes (a byte a channel) with 16 guard vectors past the last
+// column, then, in the same place, two arrays of partial sums
+template <typename T> constexpr size_t mp_lds(int nthr)
 {
-    constexpr int VEC = Elem<T>::VEC, NTHR = mp_threads(VEC), CW = VEC / 4;      // CW: code words of a vector
-    // row buffers of the windows' gradients and codes (with a guard vector past
-    // the last column), then the partial sums
-    constexpr int LD = NTHR + 16;
-    __shared__ __align__(16) unsigned char raw[3 * LD * (16 + 4 * CW)];
+    const size_t rows = (size_t)3 * (nthr + 16) * kMpVec * (sizeof(T) + 1), red = (size_t)2 * nthr * kMpVec * sizeof(float);
+    return rows > red ? rows : red;
+}
+// waves per SIMD that the registers are held to
+template <typename T> constexpr int mp_waves() { return sizeof(T) == 2 ? 5 : 4; }
+// WIDE: an image row of x or g spans 2^31 bytes or more (64-bit offsets)
+template <typename T, bool BN, bool WIDE>
+__global__ __launch_bounds__(kMpThreads, mp_waves<T>()) void k_maxpool_bwd(MaxPoolParams p, int pairs_per_chunk,
+                                                               unsigned chunks_per_image, unsigned chunks)
+{
+    using WD = MpWord<T>;
+    constexpr int VEC = kMpVec, NW = VEC / WD::N;                  // words of a vector
+    using V = MpVec<NW>;
+    extern __shared__ __align__(16) unsigned char smem[];
     __shared__ __align__(16) float par[4][kMaxPoolMaxC];           // sign(gamma), c0, c1, mean
-    vec16 (*g_s)[LD] = reinterpret_cast<vec16 (*)[LD]>(raw);                               // [3][LD]
-    uint32_t (*c_s)[CW][LD] = reinterpret_cast<uint32_t (*)[CW][LD]>(raw + 3 * LD * 16);   // [3][CW][LD]
-    float (*red)[NTHR * VEC] = reinterpret_cast<float (*)[NTHR * VEC]>(raw);               // [2][NTHR VEC]
-    static_assert(sizeof(raw) >= 2 * NTHR * VEC * sizeof(float), "partial sums");
+    const int LD = blockDim.x + 16;
+    V *g_s = reinterpret_cast<V *>(smem);                          // [3][LD]
+    uint32_t *c_s = reinterpret_cast<uint32_t *>(smem + 3 * LD * sizeof(V));      // [3][LD]
+    float *red = reinterpret_cast<float *>(smem);                  // [2][threads][VEC]
     const int C = p.c, h = p.h, w = p.w, ho = p.ho, wo = p.wo, cvec = C / VEC;
     const int tid = threadIdx.x, v = tid % cvec, ow = tid / cvec;
     const bool act = ow < wo;
-    if (tid < C) {
-        const float g = BN ? p.gamma[tid] : 1.f;
-        float c0 = 1.f, c1 = 0.f;
-        if (BN) bn_coef(g, p.beta[tid], p.mean[tid], p.rstd[tid], c0, c1);
-        par[0][tid] = g > 0.f ? 1.f : (g < 0.f ? -1.f : 0.f);
-        par[1][tid] = c0;
-        par[2][tid] = c1;
-        par[3][tid] = BN ? p.mean[tid] : 0.f;
-    }
-    // no window past the last column, ever: code 15 matches no tap
-    for (int i = tid; i < 3 * CW * 16; i += blockDim.x) c_s[i / (CW * 16)][i / 16 % CW][(int)(wo * cvec) + i % 16] = 0x0f0f0f0fu;
-    for (int i = tid; i < 3 * 16; i += blockDim.x) g_s[i / 16][wo * cvec + i % 16] = zero16();
-    __syncthreads();
-    const float *sgn = par[0] + v * VEC;
+    const T *x = reinterpret_cast<const T *>(p.x);
+    const T *gy = reinterpret_cast<const T *>(p.g);
+    T *dy = reinterpret_cast<T *>(p.y);
+    const bool in_l = ow > 0, in_r = 2 * ow + 1 < w;
+    const int cm = act ? 2 * ow : 0, cl = act && in_l ? cm - 1 : 0, cr = act ? (in_r ? cm + 1 : w - 1) : 0;
+    const int gcol = act ? ow : 0, hp = (h + 1) / 2;
+
+    // one window row: input rows 2 oh, 2 oh + 1 (columns 2 ow - 1 .. 2 ow + 1)
+    // and the window's gradient
+    struct Row { V a[3], b[3], g; };
+    using Off = std::conditional_t<WIDE, uint64_t, uint32_t>;      // byte offset in an image row
+    constexpr Off es = sizeof(T);
+    const Off x_ld = (Off)p.x_ldc * es, g_ld = (Off)p.g_ldc * es, vo = (Off)(v * VEC) * es;
+    const Off ol = (Off)cl * x_ld + vo, om = (Off)cm * x_ld + vo, orr = (Off)cr * x_ld + vo, og = (Off)gcol * g_ld + vo;
+    const uint32_t od = (uint32_t)((cm * C + v * VEC) * sizeof(T)), drow = (uint32_t)(w * C * sizeof(T));
+    auto ld = [&](const T *row, Off span, Off o) __attribute__((always_inline)) -> V {
+        if constexpr (WIDE) return *reinterpret_cast<const V *>(reinterpret_cast<const char *>(row) + o);
+        else return V::load(buf_view(row, span), o);
+    };
+    const Off xspan = (Off)(w - 1) * x_ld + (Off)C * es, gspan = (Off)(wo - 1) * g_ld + (Off)C * es;
+    // of the chunk at hand: row pairs [j0, j1) of an image
+    const T *xn, *gn;
+    T *dn;
+    int j0, j1;
+    V top[3];                                    // the input row above it
+    Row cur;
+    auto xrow = [&](int row) __attribute__((always_inline)) {
+        return xn + (int64_t)(row < 0 ? 0 : (row < h ? row : h - 1)) * w * p.x_ldc;
+    };
+    auto load_row = [&](int oh) __attribute__((always_inline)) {
+        const T *ra = xrow(2 * oh), *rb = xrow(2 * oh + 1);
+        cur.a[0] = ld(ra, xspan, ol); cur.a[1] = ld(ra, xspan, om); cur.a[2] = ld(ra, xspan, orr);
+        cur.b[0] = ld(rb, xspan, ol); cur.b[1] = ld(rb, xspan, om); cur.b[2] = ld(rb, xspan, orr);
+        cur.g = ld(gn + (int64_t)(oh < ho ? oh : ho - 1) * wo * p.g_ldc, gspan, og);
+    };
+    // (the image index is uniform: kept in a scalar, so are the row addresses)
+    auto begin = [&](unsigned ck) __attribute__((always_inline)) {
+        const int n = __builtin_amdgcn_readfirstlane((int)(ck / chunks_per_image));
+        j0 = (int)(ck - (unsigned)n * chunks_per_image) * pairs_per_chunk;
+        j1 = min(hp, j0 + pairs_per_chunk);
+        xn = x + (int64_t)n * h * w * p.x_ldc;
+        gn = gy + (int64_t)n * ho * wo * p.g_ldc;
+        dn = dy + (int64_t)n * h * w * C;
+        const T *ra = xrow(2 * j0 - 1);
+        top[0] = ld(ra, xspan, ol); top[1] = ld(ra, xspan, om); top[2] = ld(ra, xspan, orr);
+        load_row(j0);
+    };
+
+    // BN parameters, by way of LDS
+    float pg = 1.f, pb = 0.f, pm = 0.f, pr = 1.f;
+    if (BN && tid < C) { pg = p.gamma[tid]; pb = p.beta[tid]; pm = p.mean[tid]; pr = p.rstd[tid]; }
     float s1[VEC], s2[VEC], kc[VEC];
     #pragma unroll
     for (int e = 0; e < VEC; e++) { s1[e] = s2[e] = 0.f; kc[e] = BN ? bn_centre<T>(p.ctr, v * VEC + e) : 0.f; }
-    const T *x = reinterpret_cast<const T *>(p.x) + v * VEC;
-    const T *gy = reinterpret_cast<const T *>(p.g) + v * VEC;
-    T *dy = reinterpret_cast<T *>(p.y) + v * VEC;
-    const int cl = 2 * ow - 1 >= 0 ? 2 * ow - 1 : 0, cm = act ? 2 * ow : 0, cr = 2 * ow + 1 < w ? 2 * ow + 1 : w - 1;
-    const bool in_l = ow > 0, in_r = 2 * ow + 1 < w;
-    const int clc = act ? cl : 0, crc = act ? cr : 0;
+    const float *sgn = par[0] + v * VEC, *pc0 = par[1] + v * VEC, *pc1 = par[2] + v * VEC, *pmu = par[3] + v * VEC;
 
-    // first maximum of an input row's three columns (value, column 0..2 in
-    // cols, four bits a channel); the vectors of columns 2 ow, 2 ow + 1 stay
-    // with the caller
-    auto row_max = [&](const vec16 &vl, const vec16 &vm, const vec16 &vr, bool in, float *best,
-                       uint32_t &cols) __attribute__((always_inline)) {
-        float l[VEC], m_[VEC], r[VEC];
-        Elem<T>::unpack(vl, l);
-        Elem<T>::unpack(vm, m_);
-        Elem<T>::unpack(vr, r);
-        cols = 0u;
-        // (a tap outside the image: sign(gamma) x - inf, which never wins)
-        const float ol = in && in_l ? 0.f : -INFINITY, om = in ? 0.f : -INFINITY, orr = in && in_r ? 0.f : -INFINITY;
-        #pragma unroll
-        for (int e = 0; e < VEC; e++) {
-            const float sg = BN ? sgn[e] : 1.f;
-            const float kl = __builtin_fmaf(sg, l[e], ol), km = __builtin_fmaf(sg, m_[e], om);
-            const float kr = __builtin_fmaf(sg, r[e], orr);
-            float b = __builtin_fmaxf(kl, -INFINITY);              // (NaN never wins)
-            uint32_t c = km > b ? 1u : 0u;
-            b = __builtin_fmaxf(b, km);
-            c = kr > b ? 2u : c;
-            best[e] = __builtin_fmaxf(b, kr);
-            cols |= c << (4 * e);
-        }
+    // (a tap outside the image: sign(gamma) x - inf, which never wins)
+    const float off_l = in_l ? 0.f : -INFINITY, off_r = in_r ? 0.f : -INFINITY;
+    // first maximum of one channel's three columns of an input row
+    auto max3 = [&](float sg, float l, float m, float r, bool in, float &best) __attribute__((always_inline)) -> uint32_t {
+        const float omid = in ? 0.f : -INFINITY;
+        const float kl = __builtin_fmaf(sg, l, in ? off_l : -INFINITY), km = __builtin_fmaf(sg, m, omid);
+        const float kr = __builtin_fmaf(sg, r, in ? off_r : -INFINITY);
+        float b = __builtin_fmaxf(kl, -INFINITY);                  // (NaN never wins)
+        uint32_t c = km > b ? 1u : 0u;
+        b = __builtin_fmaxf(b, km);
+        c = kr > b ? 2u : c;
+        best = __builtin_fmaxf(b, kr);
+        return c;
     };
 
-    for (int64_t ck = blockIdx.x; ck < chunks; ck += gridDim.x) {
-        const int n = (int)(ck / chunks_per_image);
-        const int j0 = (int)(ck - (int64_t)n * chunks_per_image) * pairs_per_chunk;
-        const int hp = (h + 1) / 2, j1 = min(hp, j0 + pairs_per_chunk);
-        const T *xn = x + (int64_t)n * h * w * p.x_ldc;
-        const T *gn = gy + (int64_t)n * ho * wo * p.g_ldc;
-        T *dn = dy + (int64_t)n * h * w * C;
-        auto ldx = [&](int row, int col) __attribute__((always_inline)) {
-            const int rc = row < 0 ? 0 : (row < h ? row : h - 1);
-            return ldg16(xn + (int64_t)(rc * w + col) * p.x_ldc);
-        };
-        // the row above the chunk
-        float hb[VEC];
-        uint32_t hc;
-        {
-            const int r = 2 * j0 - 1;
-            const vec16 a = ldx(r, clc), b = ldx(r, cm), c = ldx(r, crc);
-            row_max(a, b, c, r >= 0, hb, hc);
-        }
-        vec16 xp[4], gp = zero16();                 // pixel block and gradient of the window row before
-        uint32_t cp[CW];
-        #pragma unroll
-        for (int i = 0; i < CW; i++) cp[i] = 0x0f0f0f0fu;
-        #pragma unroll
-        for (int i = 0; i < 4; i++) xp[i] = zero16();
-        for (int oh = j0; oh <= j1; oh++) {
-            // ---- window row oh: input rows 2 oh - 1 (carried), 2 oh, 2 oh + 1 ----
-            const int r0 = 2 * oh, r1 = 2 * oh + 1;
-            const bool wrow = oh < ho;
-            vec16 xa[3], xb[3];
-            xa[0] = ldx(r0, clc); xa[1] = ldx(r0, cm); xa[2] = ldx(r0, crc);
-            xb[0] = ldx(r1, clc); xb[1] = ldx(r1, cm); xb[2] = ldx(r1, crc);
-            const vec16 gw = ldg16(gn + (int64_t)((wrow ? oh : ho - 1) * wo + (act ? ow : 0)) * p.g_ldc);
-            float ba[VEC], bb[VEC];
-            uint32_t ca, cb, code[CW];
-            row_max(xa[0], xa[1], xa[2], r0 < h, ba, ca);
-            row_max(xb[0], xb[1], xb[2], r1 < h, bb, cb);
-            #pragma unroll
-            for (int i = 0; i < CW; i++) code[i] = 0u;
-            #pragma unroll
-            for (int e = 0; e < VEC; e++) {
-                // (a row without a value above -inf holds column 0: tap 0, as a scan that nothing wins)
-                uint32_t t = (hc >> (4 * e)) & 3u;
-                if (ba[e] > hb[e]) t = 3u + ((ca >> (4 * e)) & 3u);
-                if (bb[e] > __builtin_fmaxf(hb[e], ba[e])) t = 6u + ((cb >> (4 * e)) & 3u);
-                code[e / 4] |= t << (8 * (e % 4));
-                hb[e] = bb[e];
+    for (unsigned ck = blockIdx.x; ck < chunks; ck += gridDim.x) {
+        begin(ck);
+        if (ck == blockIdx.x) {                      // (with the first chunk's loads in flight)
+            if (tid < C) {
+                float c0 = 1.f, c1 = 0.f;
+                if (BN) bn_coef(pg, pb, pm, pr, c0, c1);
+                par[0][tid] = pg > 0.f ? 1.f : (pg < 0.f ? -1.f : 0.f);
+                par[1][tid] = c0;
+                par[2][tid] = c1;
+                par[3][tid] = pm;
             }
-            hc = cb;
+            // no window past the last column, ever: code 15 matches no tap
+            if (tid < 3 * 16) {
+                const int i = tid / 16 * LD + wo * cvec + tid % 16;
+                c_s[i] = 0x0f0f0f0fu;
+                g_s[i] = V{};
+            }
+        }
+        __syncthreads();                             // (also: the row buffers' readers of the chunk before are done)
+        // first maxima of the row above: value and column (four bits a channel)
+        float hb[VEC];
+        uint32_t hc = 0u;
+        #pragma unroll
+        for (int i = 0; i < NW; i++) {
+            float fl[WD::N], fm[WD::N], fr[WD::N];
+            WD::unpack(top[0].u[i], fl); WD::unpack(top[1].u[i], fm); WD::unpack(top[2].u[i], fr);
             #pragma unroll
-            for (int i = 0; i < CW; i++) code[i] = wrow && act ? code[i] : 0x0f0f0f0fu;
-            const int buf = oh % 3, pbuf = (oh + 2) % 3;
-            if (act) {
-                g_s[buf][tid] = gw;
+            for (int t = 0; t < WD::N; t++) {
+                const int e = i * WD::N + t;
+                hc |= max3(BN ? sgn[e] : 1.f, fl[t], fm[t], fr[t], j0 > 0, hb[e]) << (4 * e);
+            }
+        }
+        uint32_t cp = 0x0f0f0f0fu;                      // codes of the window row before
+        V pb1 = V{}, pb2 = V{}, pgv = V{};      // its second input row's pixels, its gradient
+        // finishes one input row's pixels, columns 2 ow and 2 ow + 1 (inputs x0,
+        // x1): dz(i, t, e, z0, z1) gives channel e's gradients (word i, its channel t)
+        auto finish_row = [&](int row, const V &x0, const V &x1, auto &&dz) __attribute__((always_inline)) {
+            V o0, o1;
+            #pragma unroll
+            for (int i = 0; i < NW; i++) {
+                float z0[WD::N], z1[WD::N];
                 #pragma unroll
-                for (int i = 0; i < CW; i++) c_s[buf][i][tid] = code[i];
+                for (int t = 0; t < WD::N; t++) dz(i, t, i * WD::N + t, z0[t], z1[t]);
+                if (BN) {
+                    float f0[WD::N], f1[WD::N];
+                    WD::unpack(x0.u[i], f0);
+                    WD::unpack(x1.u[i], f1);
+                    #pragma unroll
+                    for (int t = 0; t < WD::N; t++) {
+                        const int e = i * WD::N + t;
+                        f0[t] -= kc[e];
+                        f1[t] -= kc[e];
+                        z0[t] = bn_lin(f0[t], pc0[e], pc1[e]) > 0.f ? z0[t] : 0.f;
+                        z1[t] = in_r && bn_lin(f1[t], pc0[e], pc1[e]) > 0.f ? z1[t] : 0.f;
+                    }
+                    o0.u[i] = WD::pack(z0);
+                    o1.u[i] = WD::pack(z1);
+                    WD::unpack(o0.u[i], z0);
+                    WD::unpack(o1.u[i], z1);
+                    #pragma unroll
+                    for (int t = 0; t < WD::N; t++) {
+                        const int e = i * WD::N + t;
+                        const float m1 = in_r ? f1[t] - pmu[e] : 0.f;
+                        s1[e] += z0[t] + z1[t];
+                        s2[e] += __builtin_fmaf(z0[t], f0[t] - pmu[e], z1[t] * m1);
+                    }
+                } else {
+                    o0.u[i] = WD::pack(z0);
+                    o1.u[i] = WD::pack(z1);
+                }
+            }
+            const __amdgpu_buffer_rsrc_t dst = buf_view(dn + (int64_t)row * w * C, drow);
+            o0.store(dst, od);
+            o1.store(dst, in_r ? od + (uint32_t)(C * sizeof(T)) : kBufOff);
+        };
+
+        auto step = [&](int oh) __attribute__((always_inline)) {
+            // ---- window row oh: input rows 2 oh - 1 (carried), 2 oh, 2 oh + 1 ----
+            const bool wrow = oh < ho;
+            uint32_t code = 0u, nhc = 0u;
+            #pragma unroll
+            for (int i = 0; i < NW; i++) {
+                float al[WD::N], am[WD::N], ar[WD::N], bl[WD::N], bm[WD::N], br[WD::N];
+                WD::unpack(cur.a[0].u[i], al); WD::unpack(cur.a[1].u[i], am); WD::unpack(cur.a[2].u[i], ar);
+                WD::unpack(cur.b[0].u[i], bl); WD::unpack(cur.b[1].u[i], bm); WD::unpack(cur.b[2].u[i], br);
+                #pragma unroll
+                for (int t = 0; t < WD::N; t++) {
+                    const int e = i * WD::N + t;
+                    const float sg = BN ? sgn[e] : 1.f;
+                    float ba, bb;
+                    const uint32_t ca = max3(sg, al[t], am[t], ar[t], true, ba);
+                    const uint32_t cb = max3(sg, bl[t], bm[t], br[t], 2 * oh + 1 < h, bb);
+                    // (a row without a value above -inf holds column 0: tap 0, as a scan that nothing wins)
+                    uint32_t tap = (hc >> (4 * e)) & 3u;
+                    tap = ba > hb[e] ? 3u + ca : tap;
+                    tap = bb > __builtin_fmaxf(hb[e], ba) ? 6u + cb : tap;
+                    code |= tap << (8 * e);
+                    nhc |= cb << (4 * e);
+                    hb[e] = bb;
+                }
+            }
+            hc = nhc;
+            code = wrow && act ? code : 0x0f0f0f0fu;
+            V *gw_s = g_s + oh % 3 * LD + tid, *gp_s = g_s + (oh + 2) % 3 * LD + tid;
+            uint32_t *cw_s = c_s + oh % 3 * LD + tid, *cp_s = c_s + (oh + 2) % 3 * LD + tid;
+            if (act) {
+                *gw_s = cur.g;
+                *cw_s = code;
             }
             __syncthreads();
-            // ---- pixels of rows 2 j, 2 j + 1, columns 2 ow, 2 ow + 1 (j = oh - 1) ----
-            if (oh > j0 && act) {
-                const int j = oh - 1;
-                const vec16 gpr = g_s[pbuf][tid + cvec], gwr = g_s[buf][tid + cvec];
-                uint32_t cpr[CW], cwr[CW];
-                #pragma unroll
-                for (int i = 0; i < CW; i++) { cpr[i] = c_s[pbuf][i][tid + cvec]; cwr[i] = c_s[buf][i][tid + cvec]; }
-                float a00[VEC], a01[VEC], a10[VEC], a11[VEC];      // gradients of windows (j, ow), (j, ow + 1), (j + 1, ..)
-                Elem<T>::unpack(gp, a00);
-                Elem<T>::unpack(gpr, a01);
-                Elem<T>::unpack(gw, a10);
-                Elem<T>::unpack(gwr, a11);
-                float dz[4][VEC];
-                #pragma unroll
-                for (int e = 0; e < VEC; e++) {
-                    const int sh = 8 * (e % 4), q = e / 4;
-                    const uint32_t t00 = (cp[q] >> sh) & 15u, t01 = (cpr[q] >> sh) & 15u;
-                    const uint32_t t10 = (code[q] >> sh) & 15u, t11 = (cwr[q] >> sh) & 15u;
-                    // (row-major window order; an unmatched window adds zero)
-                    dz[0][e] = t00 == 4u ? a00[e] : 0.f;
-                    dz[1][e] = (t00 == 5u ? a00[e] : 0.f) + (t01 == 3u ? a01[e] : 0.f);
-                    dz[2][e] = (t00 == 7u ? a00[e] : 0.f) + (t10 == 1u ? a10[e] : 0.f);
-                    dz[3][e] = (t00 == 8u ? a00[e] : 0.f) + (t01 == 6u ? a01[e] : 0.f);
-                    dz[3][e] += t10 == 2u ? a10[e] : 0.f;
-                    dz[3][e] += t11 == 0u ? a11[e] : 0.f;
-                    dz[0][e] += 0.f;                               // (0 + -0 = 0, as a sum from zero)
+            if (act) {
+                const V gwr = gw_s[cvec];
+                const uint32_t cwr = cw_s[cvec];
+                // (an unmatched window adds zero; sums start from +0)
+                auto tap_of = [](uint32_t word, int e) __attribute__((always_inline)) { return (word >> (8 * e)) & 15u; };
+                const bool odd = oh > j0 && 2 * oh - 1 < h, even = oh < j1;
+                if (odd) {                              // windows (oh - 1, ow), (oh - 1, ow + 1), (oh, ow), (oh, ow + 1)
+                    const V gpr = gp_s[cvec];
+                    const uint32_t cpr = cp_s[cvec];
+                    finish_row(2 * oh - 1, pb1, pb2,
+                               [&](int i, int t, int e, float &z0, float &z1) __attribute__((always_inline)) {
+                        float a00[WD::N], a01[WD::N], a10[WD::N], a11[WD::N];
+                        WD::unpack(pgv.u[i], a00); WD::unpack(gpr.u[i], a01);
+                        WD::unpack(cur.g.u[i], a10); WD::unpack(gwr.u[i], a11);
+                        const uint32_t c00 = tap_of(cp, e), c01 = tap_of(cpr, e);
+                        const uint32_t c10 = tap_of(code, e), c11 = tap_of(cwr, e);
+                        z0 = (c00 == 7u ? a00[t] : 0.f) + (c10 == 1u ? a10[t] : 0.f);
+                        z1 = (c00 == 8u ? a00[t] : 0.f) + (c01 == 6u ? a01[t] : 0.f);
+                        z1 += c10 == 2u ? a10[t] : 0.f;
+                        z1 += c11 == 0u ? a11[t] : 0.f;
+                    });
                 }
-                #pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const int row = 2 * j + (i >> 1), col = 2 * ow + (i & 1);
-                    if (row < h && col < w) {
-                        float o[VEC];
-                        T *dst = dn + (int64_t)(row * w + col) * C;
-                        if (BN) {
-                            float f[VEC];
-                            Elem<T>::unpack(xp[i], f);
-                            #pragma unroll
-                            for (int e = 0; e < VEC; e++)
-                                o[e] = bn_lin(f[e] - kc[e], par[1][v * VEC + e], par[2][v * VEC + e]) > 0.f ? dz[i][e] : 0.f;
-                            const vec16 ov = Elem<T>::pack(o);
-                            stg16(dst, ov);
-                            Elem<T>::unpack(ov, o);
-                            #pragma unroll
-                            for (int e = 0; e < VEC; e++) {        // (xhat's rstd multiplies the finished sum)
-                                s1[e] += o[e];
-                                s2[e] = __builtin_fmaf(o[e], (f[e] - kc[e]) - par[3][v * VEC + e], s2[e]);
-                            }
-                        } else {
-                            stg16(dst, Elem<T>::pack(dz[i]));
-                        }
-                    }
+                if (even) {
+                    finish_row(2 * oh, cur.a[1], cur.a[2],
+                               [&](int i, int t, int e, float &z0, float &z1) __attribute__((always_inline)) {
+                        float a00[WD::N], a01[WD::N];
+                        WD::unpack(cur.g.u[i], a00); WD::unpack(gwr.u[i], a01);
+                        const uint32_t c00 = tap_of(code, e), c01 = tap_of(cwr, e);
+                        z0 = (c00 == 4u ? a00[t] : 0.f) + 0.f;              // (0 + -0 = 0, as a sum from zero)
+                        z1 = (c00 == 5u ? a00[t] : 0.f) + (c01 == 3u ? a01[t] : 0.f);
+                    });
                 }
             }
-            xp[0] = xa[1]; xp[1] = xa[2]; xp[2] = xb[1]; xp[3] = xb[2];
-            gp = gw;
-            #pragma unroll
-            for (int i = 0; i < CW; i++) cp[i] = code[i];
-        }
-        __syncthreads();                            // (the buffers' next writer is another chunk's first row)
+            pb1 = cur.b[1]; pb2 = cur.b[2]; pgv = cur.g;
+            if (oh < j1) load_row(oh + 1);
+            cp = code;
+        };
+        for (int oh = j0; oh <= j1; oh++) step(oh);
     }
+    __syncthreads();
     if (BN) {
         // threads tid = v + cvec ow hold channel vector v
         #pragma unroll
         for (int e = 0; e < VEC; e++) {
             const float rs = p.rstd[v * VEC + e];
-            red[0][tid * VEC + e] = act ? s1[e] : 0.f;
-            red[1][tid * VEC + e] = act ? s2[e] * rs : 0.f;
+            red[tid * VEC + e] = act ? s1[e] : 0.f;
+            red[(blockDim.x + tid) * VEC + e] = act ? s2[e] * rs : 0.f;
         }
         __syncthreads();
-        if (tid < C) {
-            const int cv = tid / VEC, e = tid - cv * VEC;
-            float a = 0.f, b = 0.f;
-            for (int u = cv; u < wo * cvec; u += cvec) { a += red[0][u * VEC + e]; b += red[1][u * VEC + e]; }
-            float *pr = p.part + (int64_t)blockIdx.x * 2 * C;
-            pr[tid] = a;
-            pr[C + tid] = b;
+        for (int k = tid; k < 2 * C; k += blockDim.x) {           // column k % C of sum k / C
+            const int c = k < C ? k : k - C, n_ = wo * cvec;
+            const float *col = red + ((k < C ? 0 : blockDim.x) + c / VEC) * VEC + c % VEC;
+            double a[4] = {0.0, 0.0, 0.0, 0.0};                  // (four reads in flight)
+            int u = 0;
+            for (; u + 3 * cvec < n_; u += 4 * cvec)
+                #pragma unroll
+                for (int q = 0; q < 4; q++) a[q] += col[(u + q * cvec) * VEC];
+            for (; u < n_; u += cvec) a[0] += col[u * VEC];
+            p.part[(int64_t)blockIdx.x * 2 * C + k] = (float)((a[0] + a[1]) + (a[2] + a[3]));
         }
     }
 }
@@ -1127,33 +1226,49 @@ hipError_t launch_maxpool_fwd(int dtype, const MaxPoolParams &p, bool bn, bool s
     return hipGetLastError();
 }
 
-// Threads of a workgroup: its window columns' vectors, in whole waves.
+// Threads of a workgroup: its window columns' vectors, in whole waves (at most
+// 1024: wider images are refused before the launch).
 static int mp_block(int wo, int cvec)
 {
-    const int t = (int)ceil_div((int64_t)wo * cvec, 64) * 64;
-    return t < 64 ? 64 : t;
+    const int64_t t = ceil_div((int64_t)wo * cvec, 64) * 64;
+    return t < 64 ? 64 : (t > 1024 ? 1024 : (int)t);
 }
 
-// Row pairs per chunk: the fewest of which all chunks fit the chip at once (a
-// chunk reduces one window row more than it owns, so fewer and longer chunks
-// do less, but a few chunks past the last free place cost a whole round: 40
-// images of 112 x 112 took 86 us in 560 chunks for 512 places, 64 in 480; 60
-// of 50 x 50, 46 us with 512 threads, 32 with 256 and twice the chunks).  Places:
-// 1024 threads (128 registers each) and four workgroups' LDS per CU; counted
-// for 8 channels a thread (float32 data takes two rounds).
-static int maxpool_bwd_pairs(int n, int h, int w, int c)
+// Chunks of the pooling backward.  A chunk of P row pairs costs P + 1 window
+// rows and about one more to start, and the places on the chip are filled in
+// whole rounds, so P is the best of four round counts by rounds x (P + 2).  Taken
+// as whole images wherever there are more images than places, with a nearly
+// empty last round, 520 images of 112 x 112 took 1099 us against 684 and 1103 of
+// 16 x 16 (16 channels) 84 against 31.  Places: what the waves a SIMD holds and
+// the LDS leave room for.
+struct MpPlan { int nthr, pairs, cpi; int64_t chunks, groups; };
+static MpPlan mp_plan(int dtype, int n, int h, int w, int c)
 {
-    const int64_t hp = (h + 1) / 2;
-    int per_cu = 1024 / mp_block((w - 1) / 2 + 1, c / 8);
-    per_cu = per_cu < 1 ? 1 : (per_cu > 4 ? 4 : per_cu);
-    const int64_t cpi = 256 * per_cu / n;                   // chunks per image
-    return (int)(cpi < 1 ? hp : ceil_div(hp, cpi < hp ? cpi : hp));
+    const int hp = (h + 1) / 2;
+    MpPlan best{};
+    best.nthr = mp_block((w - 1) / 2 + 1, c / kMpVec);
+    const size_t lds = (dtype == DT_BF16 ? mp_lds<bf16_t>(best.nthr) : mp_lds<float>(best.nthr)) +
+                       4 * kMaxPoolMaxC * sizeof(float);
+    const int64_t by_lds = 160 * 1024 / (int64_t)lds, by_regs = 256 * (dtype == DT_BF16 ? mp_waves<bf16_t>() : mp_waves<float>()) / best.nthr;
+    int64_t places = device_cus() * (by_lds < by_regs ? by_lds : by_regs), cost = 0;
+    if (places > kMaxPoolBwdGroups) places = kMaxPoolBwdGroups;
+    for (int r = 1; r <= 4; r++) {
+        const int64_t want = r * places / n, cut = want < 1 ? 1 : (want > hp ? hp : want);
+        const int64_t pairs = ceil_div(hp, cut), cpi = ceil_div(hp, pairs), chunks = n * cpi;
+        const int64_t t = ceil_div(chunks, places) * (pairs + 2);
+        if (r == 1 || t < cost) {
+            cost = t;
+            best.pairs = (int)pairs; best.cpi = (int)cpi; best.chunks = chunks;
+        }
+    }
+    best.groups = best.chunks < places ? best.chunks : places;
+    return best;
 }
 // workgroups, one partial row each
-int64_t maxpool_bwd_groups(int n, int h, int w, int c)
+int64_t maxpool_bwd_groups(int dtype, int n, int h, int w, int c)
 {
-    const int64_t chunks = (int64_t)n * ceil_div((h + 1) / 2, maxpool_bwd_pairs(n, h, w, c));
-    return chunks < kMaxPoolBwdGroups ? (chunks < 1 ? 1 : chunks) : kMaxPoolBwdGroups;
+    const int64_t g = mp_plan(dtype, n, h, w, c).groups;
+    return g < 1 ? 1 : g;
 }
 
 hipError_t launch_maxpool_bwd(int dtype, const MaxPoolParams &p, bool bn, hipStream_t s)
@@ -1163,17 +1278,23 @@ hipError_t launch_maxpool_bwd(int dtype, const MaxPoolParams &p, bool bn, hipStr
         p.c > kMaxPoolMaxC || p.wo > kMaxPoolMaxWo || cvec < 1 || (kThreads % cvec) ||
         p.ho != (p.h - 1) / 2 + 1 || p.wo != (p.w - 1) / 2 + 1)
         return hipErrorInvalidValue;
-    const unsigned g = (unsigned)maxpool_bwd_groups(p.n, p.h, p.w, p.c);
     const double e = dtype == DT_BF16 ? 2.0 : 4.0, m = (double)p.n * p.h * p.w;
     TraceScope tr(KC_SWEEP, KID_MAXPOOL, s, e * p.c * ((bn ? 2.0 : 1.0) * m + (double)p.n * p.ho * p.wo), 0.0);
-    const int pairs = maxpool_bwd_pairs(p.n, p.h, p.w, p.c), cpi = (int)ceil_div((p.h + 1) / 2, pairs);
-    const int64_t chunks = (int64_t)p.n * cpi;
-    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(g), dim3((unsigned)mp_block(p.wo, cvec)), 0, s, p, pairs, cpi, chunks); };
-    if (dtype == DT_BF16) {
-        if (bn) go(k_maxpool_bwd<bf16_t, true>); else go(k_maxpool_bwd<bf16_t, false>);
-    } else {
-        if (bn) go(k_maxpool_bwd<float, true>); else go(k_maxpool_bwd<float, false>);
-    }
+    const MpPlan pl = mp_plan(dtype, p.n, p.h, p.w, p.c);
+    const int64_t lim = (int64_t)1 << 31, es = dtype == DT_BF16 ? 2 : 4;
+    const bool wide = ((p.w - 1) * p.x_ldc + p.c) * es >= lim || ((p.wo - 1) * p.g_ldc + p.c) * es >= lim;
+    if (pl.chunks >= lim) return hipErrorInvalidValue;           // (n < 2^31 and n h w <= 2^31: never)
+    auto go = [&](auto kern, size_t lds) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)pl.groups), dim3((unsigned)pl.nthr), lds, s, p, pl.pairs, (unsigned)pl.cpi,
+                           (unsigned)pl.chunks);
+    };
+    auto go_t = [&](auto t) {
+        using T = decltype(t);
+        const size_t lds = mp_lds<T>(pl.nthr);
+        if (wide) { if (bn) go(k_maxpool_bwd<T, true, true>, lds); else go(k_maxpool_bwd<T, false, true>, lds); }
+        else { if (bn) go(k_maxpool_bwd<T, true, false>, lds); else go(k_maxpool_bwd<T, false, false>, lds); }
+    };
+    if (dtype == DT_BF16) go_t(bf16_t()); else go_t(float());
     return hipGetLastError();
 }
 

@@ -125,3 +125,20 @@ def test_pooled_gradient_sums_round_no_further(B):
     B.bnr_bwd_data(B.conv_desc(n, h, w, ci, co, 1, ci, co, B.dtype_code(x)), x, bn, wt, B.grad_avgpool2(g), dg, db, dy)
     e = _sum_errors(dg, db, dy, x, bn)
     assert e[0] <= 1.65e-9 and e[1] <= 5.2e-10, e
+# (bounds: between what the kernel has, 5.7e-10 to 6.8e-10, and the float32
+# chains of single pixels and of columns, 9.7e-10 to 1.2e-9; the kernel that
+# scanned every window has 6.8e-10 to 9.4e-10)
+@pytest.mark.parametrize("bf16,n,h,w,c,bound", [
+    (True, 20, 95, 95, 64, 8.0e-10),
+    (True, 60, 50, 50, 64, 9.0e-10),
+    (False, 20, 95, 95, 64, 6.7e-10),
+    (False, 60, 50, 50, 64, 7.4e-10),
+])
+def test_maxpool_backward_sums_round_no_further(B, bf16, n, h, w, c, bound):
+    ho, wo = (h - 1) // 2 + 1, (w - 1) // 2 + 1
+    x, g = dev(synth.normal(6, "x", (n, h, w, c), bf16=bf16), bf16), dev(synth.normal(6, "g", (n, ho, wo, c), bf16=bf16), bf16)
+    bn = _bn_of(B, x, 6)
+    dy, dg, db = torch.empty_like(x), torch.empty(c, device="cuda"), torch.empty(c, device="cuda")
+    B.bnr_maxpool_bn_bwd(x, bn, g, dy, n, h, w, dg, db)
+    e = _sum_errors(dg, db, dy, x, bn)
+    assert e[0] <= bound and e[1] <= (2.4e-10 if bf16 else 5.5e-10), e

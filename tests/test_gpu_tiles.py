@@ -150,6 +150,9 @@ def test_conv3x3_nan_and_inf_stay_local(B):
     (True, 1100, 5, 4, 8),      # more images than places: whole images as chunks
     (True, 33, 6, 66, 64),      # workgroups of five waves
     (True, 115, 18, 5, 32),     # chunks of two, the last of an image one pair
+    (True, 2500, 5, 4, 8),      # more images than workgroups: several chunks each
+    (False, 300, 21, 30, 64),   # more images than places: images split
+    (True, 70, 9, 128, 64),     # the widest workgroups, one on a CU
 ])
 def test_maxpool_bwd_chunks(B, bf16, n, h, w, c):
     """Small whole numbers (many ties) and whole-number gradients: every sum is
@@ -174,6 +177,23 @@ def test_maxpool_bwd_chunks(B, bf16, n, h, w, c):
     np.testing.assert_array_equal(host(dz), refy)
     np.testing.assert_allclose(host(db), refy.reshape(-1, c).sum(0), rtol=0, atol=1e-6 * np.abs(refy).sum() / c + 1e-6)
     np.testing.assert_allclose(host(dg), (refy * x).reshape(-1, c).sum(0), rtol=0, atol=4e-6 * np.abs(refy).sum() / c + 1e-6)
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+def test_maxpool_bwd_rows_past_2_gib(B, bf16):
+    """An input view whose image rows span more than 2^31 bytes (64-bit offsets in a row)."""
+    h, w, c = 3, 2, 8
+    ldc = (1 << 31) // (2 if bf16 else 4)
+    rng = np.random.default_rng(5)
+    x = rng.integers(-3, 4, size=(1, h, w, c)).astype(np.float64)
+    gy = rng.integers(-8, 9, size=(1, 2, 1, c)).astype(np.float64)
+    buf = torch.empty((h * w - 1) * ldc + c, dtype=torch.bfloat16 if bf16 else torch.float32, device="cuda")
+    xd = buf.as_strided((1, h, w, c), (h * w * ldc, w * ldc, ldc, 1))
+    xd.copy_(dev(x, bf16))
+    dz = torch.full((1, h, w, c), 9.0, dtype=xd.dtype, device="cuda")
+    B.bnr_maxpool_bn_bwd(xd, None, dev(gy, bf16), dz, 1, h, w)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(host(dz), P.maxpool_bwd(x, gy, 3, 2, 1))
 
 
 @pytest.mark.parametrize("n,h,w,c_in", [(1, 1, 1, 3), (3, 9, 255, 3), (2, 256, 256, 4), (700, 5, 6, 1)])
