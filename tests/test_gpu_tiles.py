@@ -96,11 +96,76 @@ def _layer(B, bf16, k, n, h, w, ci, co, seed=11, pad_in=0, pad_out=0):
     (3, 37, 2, 128, 8),         # narrow rows: many rows of the padded grid in a tile
     (4, 13, 9, 48, 40),         # two K and two N slices, ragged
     (2, 9, 30, 24, 96),         # one K slice, a ragged fourth N slice
-    (40, 14, 14, 128, 32),      # several tiles per workgroup, ranges that cross images
+    (40, 14, 14, 128, 32),      # one-tile ranges that cross images
     (1, 300, 2, 32, 64),        # tall images
+    (76, 32, 8, 40, 24),        # two 64-row tiles per workgroup, the second one short
+    (60, 30, 26, 16, 16),       # two 128-row tiles
+    (90, 24, 20, 40, 8),        # four 64-row tiles: the pipelined loop
+    (40, 56, 40, 8, 8),         # three 128-row tiles: the pipelined loop
 ])
 def test_conv3x3_tiles_bf16(B, n, h, w, ci, co):
     _layer(B, True, 3, n, h, w, ci, co, pad_in=8, pad_out=8)
+
+
+@pytest.mark.parametrize("n,h,w,ci,co", [
+    (90, 24, 20, 40, 8),        # four 64-row tiles a workgroup, two K slices
+    (40, 56, 40, 8, 8),         # three 128-row tiles
+    (60, 22, 40, 128, 32),      # four 64-row tiles, four K slices (forward), four N slices (data gradient)
+    (64, 22, 30, 64, 64),       # three 64-row tiles, two slices each
+])
+def test_conv3x3_long_ranges_equal_short_ones(B, n, h, w, ci, co):
+    """Every form of the bf16 3x3 CONV gives each image of a batch (ranges of
+    many tiles: the pipelined loop) bit for bit what it gives the image alone
+    (ranges of one or two tiles, without the loop)."""
+    x = dev(synth.normal(7, "x", (n, h, w, ci + 8), bf16=True), True)[..., :ci]
+    g = dev(synth.normal(7, "g", (n, h, w, co + 8), bf16=True), True)[..., :co]
+    xo = dev(synth.normal(7, "xo", (n, h, w, co), bf16=True), True)
+    old = dev(synth.normal(7, "old", (n, h, w, ci), bf16=True), True)
+    wt = dev(synth.conv_weight(7, "w", 3, ci, co, True), True)
+    p1 = synth.bn_params(7, "bn", ci)
+    gam = f32dev(p1["gamma"])
+    gam[ci // 2] = 0.0                                      # its vector reads x in the z form
+    mk = lambda v, c: torch.full((c,), v, device="cuda")
+    bn = lambda: B.BN(gam, f32dev(p1["beta"]), 1e-5, mk(0.05, ci), mk(1.0, ci), mk(1.1, ci))
+    bo = B.BN(mk(1.0, co), mk(0.0, co), 1e-5, mk(0.1, co), mk(1.0, co), mk(0.9, co))
+    al, be = f32dev(synth.normal(7, "al", (co,)) * 0.1), f32dev(synth.normal(7, "be", (co,)) * 0.1)
+
+    def forms(sl):
+        xs, gs, xos, olds = x[sl], g[sl], xo[sl], old[sl].clone()
+        nn = xs.shape[0]
+        desc = B.desc_for(xs, gs, 3, nn, h, w)
+        new = lambda c: torch.empty((nn, h, w, c), dtype=x.dtype, device="cuda")
+        f32 = lambda c: torch.empty(c, device="cuda")
+        o = {}
+        yd = new(co + 8)                                    # (the descriptor's output stride)
+        o["plain"] = yd[..., :co]
+        B.bnr_conv_fwd(desc, xs, wt, o["plain"])
+        o["bn"] = new(co + 8)[..., :co]
+        B.bnr_bn_relu_conv_fwd(desc, xs, bn(), wt, o["bn"])
+        o["bn stats"] = new(co + 8)[..., :co]
+        B.bnr_bn_relu_conv_fwd(desc, xs, bn(), wt, o["bn stats"], B.BN.stats_only(co, x.device))
+        o["saved z"], o["z out"], o["z stats"] = new(ci), new(co + 8)[..., :co], new(co + 8)[..., :co]
+        B.bnr_bn_relu_conv_fwd_o2(desc, xs, bn(), wt, o["z out"], o["saved z"])
+        B.bnr_bn_relu_conv_fwd_o2(desc, xs, bn(), wt, o["z stats"], o["saved z"], B.BN.stats_only(co, x.device))
+        dense, split = B.grad_dense(gs), B.grad_split(gs, xos, bo, al, be)
+        for name, src in (("dense", dense), ("split", split)):
+            o[name + " dy"], o[name + " z dy"], o[name + " dx"], o[name + " dx add"] = new(ci), new(ci), new(ci), olds.clone()
+            B.bnr_bwd_data(desc, xs, bn(), wt, src, f32(ci), f32(ci), o[name + " dy"])
+            B.bnr_bwd_fused_o2(desc, xs, bn(), o["saved z"], wt, src, torch.empty((3, 3, ci, co), device="cuda"), f32(ci),
+                               f32(ci), o[name + " z dy"])
+            B.bnr_bwd_data(desc, xs, None, wt, src, dx=o[name + " dx"])
+            B.bnr_bwd_data(desc, xs, None, wt, src, dx=o[name + " dx add"], dx_accumulate=True)
+        y = torch.relu(xs.float() - 0.1).to(x.dtype).contiguous()
+        o["relu mask"] = new(ci)
+        B.bnr_reference_path(B.MODE_RCF, True, desc, xs, bn(), wt, y, g=gs, dy=o["relu mask"],
+                             dw=torch.empty((3, 3, ci, co), device="cuda"), dgamma=f32(ci), dbeta=f32(ci), dx=new(ci))
+        torch.cuda.synchronize()
+        return o
+
+    whole = forms(slice(0, n))
+    for i in (0, 1, n // 3, n // 2, n - 2, n - 1):
+        for name, t in forms(slice(i, i + 1)).items():
+            assert torch.equal(whole[name][i], t[0]), "%s, image %d" % (name, i)
 
 
 @pytest.mark.parametrize("k,n,h,w,ci,co", [
