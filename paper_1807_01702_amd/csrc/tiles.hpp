@@ -168,8 +168,9 @@ inline WgTrPlan wgrad_tr_plan(int64_t m, int n, int h, int w, int c_in, int c_ou
 // COT output channels, chunks of 32 pixels; 3x3: 32 input x COT output
 // channels and all nine taps, chunks of R image rows of PW = W + 2 padded
 // positions (KQ <= 64 of them), Z rows with a halo as in wgrad_tr_plan.  The
-// split count aims at two workgroups per CU; partial tiles stay below the
-// operand bytes, or below kWgTrSmallPartBytes for small operands (as there).
+// split count aims at two workgroups per CU, at one where that leaves a split
+// fewer than four chunks (3x3: three); partial tiles stay below the operand bytes, or
+// below kWgTrSmallPartBytes for small operands (as there).
 constexpr int kWfKQ1 = 32, kWfKQ3 = 64;
 inline WgTrPlan wgrad_f32_plan(int64_t m, int n, int h, int w, int c_in, int c_out, int k)
 {
@@ -195,7 +196,14 @@ inline WgTrPlan wgrad_f32_plan(int64_t m, int n, int h, int w, int c_in, int c_o
         p.chunks_per_image = 0;
         p.nchunks = ceil_div(m, kWfKQ1);
     }
-    int64_t s = ceil_div(512, (int64_t)p.ci_tiles * p.co_tiles);
+    // (whole rounds: 532 workgroups for 512 places took 396 us against 265; with
+    // one to three chunks a split the sum over the splits costs more than the
+    // second workgroup of a CU gives: 1x1, 40 images of 8 x 51, 64 -> 112
+    // channels, 27.6 us in 510 splits, 20.7 in 255; 8 of 24 x 31, 256 -> 56, 19.0
+    // and 16.3)
+    const int64_t tiles = (int64_t)p.ci_tiles * p.co_tiles;
+    int64_t s = 512 / tiles, half = 256 / tiles, few = p.nchunks / (k == 1 ? 4 : 3);
+    if (s > half && s > few) s = half > few ? half : few;
     const int64_t dw_bytes = (int64_t)k * k * c_in * c_out * 4;
     int64_t in_bytes = m * (int64_t)(c_in + c_out) * 4;
     if (in_bytes < kWgTrSmallPartBytes) in_bytes = kWgTrSmallPartBytes;
