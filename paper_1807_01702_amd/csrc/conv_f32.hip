@@ -32,6 +32,19 @@ namespace bnr {
 
 constexpr int kF32BM = 64;
 constexpr int f32_bk(int taps) { return taps == 9 ? 16 : 64; }      // K channels of a chunk
+// Row pitch of the staged rows (floats).  1x1: no padding, the sixteen 16-byte
+// blocks of a row are permuted by the row number instead (f32_at), which leaves
+// room for four workgroups per CU up to K = 1024: with padded rows and four
+// coefficient arrays three fitted past K = 384, and 40 images of 28 x 28 took
+// 58.4 us forward at 416 -> 128 channels (39.3 at 320 -> 128), 46.4 this way.
+constexpr int f32_pitch(int taps) { return taps == 9 ? f32_bk(taps) + 4 : f32_bk(taps); }
+template <int TAPS> __device__ __forceinline__ int f32_at(int row, int c)
+{
+    return row * f32_pitch(TAPS) + (TAPS == 9 ? c : c ^ (4 * (row & 15)));
+}
+// per-channel coefficients in LDS (floats): c0, c1, (deferred gradient) c2 and the
+// centre, where there is none four zeros
+static size_t f32_coefs(const RowsParams &p) { return (size_t)(p.pro == PRO_BNGRAD ? 3 : 2) * p.K + (p.p_ctr ? p.K : 4); }
 // prologue kinds: FP_ONE (none, BN+ReLU, ReLU or the pooling gradient, chosen
 // at run time), FP_BNGRAD and FP_BNADD (a second operand: the deferred BN input
 // gradient; BN + identity + ReLU), FP_POOL (four input pixels a row).  With a
@@ -55,7 +68,7 @@ template <int TAPS, int WN, int FP, int EK, bool WT>
 __global__ __launch_bounds__(kThreads, f32_waves(TAPS, WN, FP, WT)) void k_conv_f32(RowsParams p)
 {
     using M = Mfma<float>;
-    constexpr int BK = f32_bk(TAPS), PITCH = BK + 4;
+    constexpr int BK = f32_bk(TAPS), PITCH = f32_pitch(TAPS);
     constexpr int WM = 4 / WN, TM = kF32BM / 16 / WM;
     constexpr int HALO = TAPS == 9 ? kRowsMaxW3 + 1 : 0;
     constexpr int VPR = BK / 4, RPS = kThreads / VPR;         // vectors per staged row; rows per pass
@@ -79,7 +92,9 @@ __global__ __launch_bounds__(kThreads, f32_waves(TAPS, WN, FP, WT)) void k_conv_
     const int p0 = mt * kF32BM, n0 = blockIdx.y * 16 * WN;
     const int halo = TAPS == 9 ? W + 1 : 0, arows = kF32BM + 2 * halo;
     float *As = reinterpret_cast<float *>(smem);                  // [2][arows][PITCH]
-    float *coef = As + 2 * arows * PITCH;                     // [4][K]: c0, c1, c2, centre
+    float *coef = As + 2 * arows * PITCH;                     // [f32_coefs][K]: c0, c1, c2, centre
+    constexpr bool C2 = FP == FP_BNGRAD;
+    float *cen = coef + (C2 ? 3 : 2) * K;
     const bool bnr = FP == FP_POOL || FP == FP_BNADD || (FP == FP_ONE && p.pro == PRO_BNRELU);
     const bool pool = FP == FP_ONE && p.pro == PRO_POOLUP, relu = FP == FP_ONE && p.pro == PRO_RELU;
 
@@ -138,7 +153,9 @@ __global__ __launch_bounds__(kThreads, f32_waves(TAPS, WN, FP, WT)) void k_conv_
         if (bnr || FP == FP_BNGRAD)
             #pragma unroll
             for (int e = 0; e < 4; e++) {
-                k0[e] = coef[cc + e]; k1[e] = coef[K + cc + e]; k2[e] = coef[2 * K + cc + e]; kc[e] = coef[3 * K + cc + e];
+                k0[e] = coef[cc + e]; k1[e] = coef[K + cc + e];
+                k2[e] = C2 ? coef[2 * K + cc + e] : 0.f;
+                kc[e] = cen[(p.p_ctr ? cc : 0) + e];
             }
         #pragma unroll
         for (int j = 0; j < NA; j++) {
@@ -190,7 +207,7 @@ __global__ __launch_bounds__(kThreads, f32_waves(TAPS, WN, FP, WT)) void k_conv_
                       Elem<float>::pack(f));
             }
             if (TAPS == 1 || ar0 + j * RPS < arows)
-                *reinterpret_cast<vec16 *>(dst + (ar0 + j * RPS) * PITCH + av) = Elem<float>::pack(f);
+                *reinterpret_cast<vec16 *>(dst + f32_at<TAPS>(ar0 + j * RPS, av)) = Elem<float>::pack(f);
         }
     };
 
@@ -219,6 +236,7 @@ __global__ __launch_bounds__(kThreads, f32_waves(TAPS, WN, FP, WT)) void k_conv_
     for (int s = 0; s + 1 < ND; s++) load_w(0, s, wb[s]);
     if (bnr || FP == FP_BNGRAD) {
         const float inv_m = 1.0f / (float)m;
+        if (!p.p_ctr && tid < 4) cen[tid] = 0.f;
         for (int c = tid; c < K; c += kThreads) {
             float c0, c1, c2 = 0.f;
             const float kc = bn_centre<float>(p.p_ctr, c);
@@ -230,7 +248,9 @@ __global__ __launch_bounds__(kThreads, f32_waves(TAPS, WN, FP, WT)) void k_conv_
             } else {
                 bn_coef(p.p_gamma[c], p.p_beta[c], p.p_mean[c], p.p_rstd[c], c0, c1);
             }
-            coef[c] = c0; coef[K + c] = c1; coef[2 * K + c] = c2; coef[3 * K + c] = kc;
+            coef[c] = c0; coef[K + c] = c1;
+            if (C2) coef[2 * K + c] = c2;
+            if (p.p_ctr) cen[c] = kc;
         }
     }
     // pixels of this lane's accumulators, and (3x3) the taps inside the image
@@ -257,7 +277,7 @@ __global__ __launch_bounds__(kThreads, f32_waves(TAPS, WN, FP, WT)) void k_conv_
     __syncthreads();
 
     const int nch = (K + BK - 1) / BK;
-    const int abase = (wm * TM * 16 + l16 + halo) * PITCH + 4 * q4;
+    const int arow = wm * TM * 16 + l16 + halo;
     for (int ch = 0; ch < nch; ch++) {
         const float *src = As + (ch & 1) * arows * PITCH;
         if (ch + 1 < nch) load_chunk(ch + 1);
@@ -267,10 +287,11 @@ __global__ __launch_bounds__(kThreads, f32_waves(TAPS, WN, FP, WT)) void k_conv_
         float4 a[2][TM];
         auto load_a = [&](int s, float4 *dst) __attribute__((always_inline)) {
             const int tap = s % TAPS, kg = s / TAPS;
-            const int off = TAPS == 9 ? ((tap / 3 - 1) * W + tap % 3 - 1) * PITCH : 0;
+            const int off = TAPS == 9 ? (tap / 3 - 1) * W + tap % 3 - 1 : 0;
+            const float *ap = src + f32_at<TAPS>(arow + off, 4 * q4 + kg * 16);       // (16 rows on: the same permutation)
             #pragma unroll
             for (int i = 0; i < TM; i++)
-                dst[i] = *reinterpret_cast<const float4 *>(src + abase + off + i * 16 * PITCH + kg * 16);
+                dst[i] = *reinterpret_cast<const float4 *>(ap + i * 16 * PITCH);
         };
         load_a(0, a[0]);
         #pragma unroll
@@ -400,7 +421,7 @@ static hipError_t run_f32(const RowsParams &p, hipStream_t s)
 {
     const int arows = kF32BM + (TAPS == 9 ? 2 * (p.w + 1) : 0);
     // statistics scratch: two arrays of 16 WM rows of 16 WN floats (8 KB)
-    const size_t lds = ((size_t)2 * arows * (f32_bk(TAPS) + 4) + 4 * (size_t)p.K) * sizeof(float);
+    const size_t lds = ((size_t)2 * arows * f32_pitch(TAPS) + f32_coefs(p)) * sizeof(float);
     const double m = (double)p.m, e = 4.0;
     double a = m * p.K;
     if (FP == FP_BNGRAD || p.side) a *= 2.0;

@@ -175,6 +175,10 @@ def test_conv3x3_long_ranges_equal_short_ones(B, n, h, w, ci, co):
     (1, 5, 13, 5, 300, 68),     # ten K chunks (the last of 12 channels), two column tiles of 64
     (1, 1, 33, 2, 8, 132),      # one chunk, three column tiles
     (1, 40, 16, 15, 160, 128),  # weight gradient: several 32-pixel chunks per split
+    (1, 2, 9, 7, 832, 36),      # thirteen K chunks
+    (1, 1, 5, 5, 1100, 12),     # more coefficients than leave room for four workgroups
+    (1, 40, 8, 51, 64, 112),    # weight gradient: half the splits (two chunks each)
+    (3, 12, 24, 29, 232, 40),   # weight gradient: eight column tiles, whole rounds of splits
     (3, 2, 1, 1, 4, 8),         # one pixel: the centre tap only
     (3, 1, 5, 62, 32, 32),      # widest rows: the longest halo, one row per weight-gradient chunk
     (3, 3, 7, 6, 20, 36),       # ragged channels, eight rows of positions in a chunk
