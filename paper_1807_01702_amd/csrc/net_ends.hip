@@ -254,7 +254,7 @@ __device__ __forceinline__ bf16x8 tr_pair(const bf16_t *lo, const bf16_t *hi)
     return __builtin_bit_cast(bf16x8, v);
 }
 
-template <int GS>
+template <int GS, int MAXW>
 __global__ __launch_bounds__(kThreads, 2) void k_stem_wgrad(StemParams p)
 {
     using M = Mfma<bf16_t>;
@@ -294,8 +294,9 @@ __global__ __launch_bounds__(kThreads, 2) void k_stem_wgrad(StemParams p)
     // kSIR x RPX staged pixels, gradient slots (pixel tid / 8 + 32 j, channel
     // vector tid % 8).  Their rows and columns are split once; an item is a
     // base pointer and range tests (loads at a clamped position, zeroed when
-    // they are written to LDS).
-    constexpr int NI = (kSIR * (kStemMaxW + 6) + kThreads - 1) / kThreads, NG = (kStemRows * (kStemMaxW / 2) + 31) / 32;
+    // they are written to LDS).  MAXW: the widest image the slots are for (images
+    // of up to 64 in slots for 256 took up to 5% more than the sequence).
+    constexpr int NI = (kSIR * (MAXW + 6) + kThreads - 1) / kThreads, NG = (kStemRows * (MAXW / 2) + 31) / 32;
     constexpr int kNever = -(1 << 28);
     int ir[NI], io[NI];
     #pragma unroll
@@ -1191,8 +1192,9 @@ hipError_t launch_stem_wgrad(int dtype, const StemParams &p, int gsrc, hipStream
         const int64_t items = (int64_t)p.n * ((p.ho + kStemRows - 1) / kStemRows);
         const unsigned g = (unsigned)stem_groups(items);
         const size_t lds = stem_lds(p.wo, true);
-        if (gsrc == GB_BNGRAD) hipLaunchKernelGGL(k_stem_wgrad<GB_BNGRAD>, dim3(g), dim3(kThreads), lds, s, p);
-        else hipLaunchKernelGGL(k_stem_wgrad<GB_DENSE>, dim3(g), dim3(kThreads), lds, s, p);
+        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), lds, s, p); };
+        if (gsrc == GB_BNGRAD) { if (p.w <= 64) go(k_stem_wgrad<GB_BNGRAD, 64>); else go(k_stem_wgrad<GB_BNGRAD, kStemMaxW>); }
+        else { if (p.w <= 64) go(k_stem_wgrad<GB_DENSE, 64>); else go(k_stem_wgrad<GB_DENSE, kStemMaxW>); }
     } else {
         const unsigned g = (unsigned)ceil_div((int64_t)nw, kThreads);
         if (gsrc == GB_BNGRAD) hipLaunchKernelGGL(k_stem_wgrad_f32<GB_BNGRAD>, dim3(g), dim3(kThreads), 0, s, p);

@@ -265,11 +265,12 @@ def test_maxpool_bwd_rows_past_2_gib(B, bf16):
     np.testing.assert_array_equal(host(dz), P.maxpool_bwd(x, gy, 3, 2, 1))
 
 
-@pytest.mark.parametrize("n,h,w,c_in", [(1, 1, 1, 3), (3, 9, 255, 3), (2, 256, 256, 4), (700, 5, 6, 1)])
+@pytest.mark.parametrize("n,h,w,c_in", [(1, 1, 1, 3), (3, 9, 255, 3), (2, 256, 256, 4), (700, 5, 6, 1), (3, 11, 64, 3),
+                                        (3, 11, 65, 3)])
 def test_stem_wgrad_items(B, n, h, w, c_in):
     """Weight gradient of the first CONV at the ends of its staging slots: one
     output pixel, the widest image (all slots), an odd last row, more items
-    than workgroups.  Whole numbers: exact in bf16 and in float32 sums."""
+    than workgroups, the widest image of the kernel with few slots and one more.  Whole numbers: exact in bf16 and in float32 sums."""
     rng = np.random.default_rng(6)
     ho, wo = (h - 1) // 2 + 1, (w - 1) // 2 + 1
     img = np.zeros((n, h, w, 4))
