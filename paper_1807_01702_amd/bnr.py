@@ -198,11 +198,13 @@ def _ptr(t):
 def _stream():
     # the current stream of the current device as a raw handle, without building
     # the torch.cuda.Stream object around it (4 us a call, a quarter of a small
-    # call's host time)
+    # call's host time) where torch has that function
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
     return _raw_stream(_current_device())
 
 
-_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
+_raw_stream, _current_device = getattr(torch._C, "_cuda_getCurrentRawStream", None), torch.cuda.current_device
 
 
 _ws_cache = {}

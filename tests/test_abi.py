@@ -219,3 +219,18 @@ def test_static_scratch_entry_point_limit(B):
     assert status(256, 64, 64, 256, 256, 1, B.BNR_F32) == "BNR_ERR_WORKSPACE"
     d = _desc(B)
     assert B.STATUS[f(ctypes.byref(d), A, None, A + 0x1000, A + 0x2000, None, None)] == "BNR_ERR_NULL"   # x_bn
+
+
+def test_binding_imports_on_a_torch_without_the_raw_stream_function():
+    """The raw stream handle comes from a private function of torch: without it
+    the binding imports and takes the public way."""
+    import subprocess
+    import sys
+    code = ("import torch\n"
+            "if hasattr(torch._C, '_cuda_getCurrentRawStream'): del torch._C._cuda_getCurrentRawStream\n"
+            "from paper_1807_01702_amd import bnr\n"
+            "class S: cuda_stream = 4711\n"
+            "torch.cuda.current_stream = lambda: S\n"
+            "assert bnr._stream() == 4711\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
