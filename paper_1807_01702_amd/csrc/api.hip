@@ -283,8 +283,11 @@ void fill_rows(RowsParams &rp, const bnr_conv_desc *d, int K, int N)
 }
 
 // Runs the CONV GEMM of rp (forward when transpose = 0, data gradient when 1)
-// with the persistent 1x1 kernel when it applies, else packs the weights and
-// runs the tiled kernel.  *rows = statistics partial rows written.
+// with the first kernel that takes it: bf16 data, the pooled-gradient kernel,
+// the persistent 1x1 or 3x3 kernel; float32 data, the kernel on the caller's
+// weights; else (operands of 2 GiB and more, wide CONVs) the tiled kernel, which
+// packs the weights unless it can read them as they are.  *rows = statistics
+// partial rows written.
 bnr_status launch_conv_any(RowsParams &rp, const bnr_conv_desc *d, const void *w, int transpose, void *wpack,
                            int64_t *rows, hipStream_t s)
 {
@@ -295,13 +298,13 @@ bnr_status launch_conv_any(RowsParams &rp, const bnr_conv_desc *d, const void *w
         TRY_HIP(launch_conv_poolup(rp, s), "conv data gradient");
         return BNR_OK;
     }
-    if (rp.taps == 1 && conv1x1_supported(rp.dtype, rp.K, rp.N, rp.epi)) {
+    if (conv1x1_supported(rp)) {
         rp.wraw = w;
         rp.wtrans = transpose;
         TRY_HIP(launch_conv1x1(rp, s, rows), transpose ? "conv data gradient" : "conv forward");
         return BNR_OK;
     }
-    if (rp.taps == 9 && rp.pro != PRO_POOLUP && !rp.e_scale && conv3x3_supported(rp.dtype, rp.K, rp.N, rp.h, rp.w)) {
+    if (conv3x3_supported(rp)) {
         rp.wraw = w;
         rp.wtrans = transpose;
         *rows = conv3x3_partial_rows(rp.m);

@@ -563,9 +563,20 @@ static int p1_group_cols(int K, int N)
     return 32;
 }
 
-bool conv1x1_supported(int dtype, int K, int N, int epi)
+// (operands past 32-bit offsets: conv_rows)
+bool conv1x1_supported(const RowsParams &p)
 {
-    if (dtype != DT_BF16 || K > 256 || N < 1 || N > kP1MaxN || (N > 256 && epi != EPI_BNBWD)) return false;
+    const int K = p.K, N = p.N;
+    if (p.dtype != DT_BF16 || p.taps != 1 || p.pro == PRO_POOLUP || K > 256 || N < 1 || N > kP1MaxN ||
+        (N > 256 && p.epi != EPI_BNBWD))
+        return false;
+    // 32-bit pixel indices and raw-buffer operand views: every span below 2^31 bytes
+    const int64_t lim = (int64_t)1 << 31;
+    const int64_t arows = p.pro == PRO_BNRELU_POOL ? 4 * p.m : p.m;
+    if (arows >= (lim >> 1) || (arows * p.a_ldc + K) * 2 >= lim || (p.m * p.y_ldc + N) * 2 >= lim ||
+        (p.a2 && (p.m * p.a2_ldc + K) * 2 >= lim) || (p.ex && (p.m * p.ex_ldc + N) * 2 >= lim) ||
+        (p.ex2 && (p.m * p.ex2_ldc + N) * 2 >= lim) || (p.side && (p.m * p.side_ldc + K) * 2 >= lim))
+        return false;
     const P1Geom g = p1_geom(K, p1_group_cols(K, N));
     if (g.lds > kP1MaxLds) return false;
     if ((int64_t)kP1BM * (g.KP / 8) > (int64_t)kP1NV * kP1Threads) return false;      // A tile registers
@@ -680,7 +691,7 @@ static hipError_t run_p1_ek(const RowsParams &p, const P1Geom &g, int ek, hipStr
 
 hipError_t launch_conv1x1(const RowsParams &p, hipStream_t s, int64_t *rows)
 {
-    if (!p.a || !p.wraw || !p.y || p.taps != 1 || !conv1x1_supported(p.dtype, p.K, p.N, p.epi)) return hipErrorInvalidValue;
+    if (!p.a || !p.wraw || !p.y || p.m < 1 || !conv1x1_supported(p)) return hipErrorInvalidValue;
     if (p.pro == PRO_BNRELU && (!p.p_mean || !p.p_gamma || !p.p_rstd || !p.p_beta)) return hipErrorInvalidValue;
     if (p.pro == PRO_BNGRAD && (!p.a2 || !p.p_mean || !p.p_rstd ||
                                 (p.p_split ? (!p.p_alpha || !p.p_betap) : (!p.p_gamma || !p.p_dbeta || !p.p_dgamma))))
@@ -688,7 +699,6 @@ hipError_t launch_conv1x1(const RowsParams &p, hipStream_t s, int64_t *rows)
     if ((p.epi == EPI_STATS || p.epi == EPI_BNBWD) && !p.part) return hipErrorInvalidValue;
     if (p.epi == EPI_BNBWD && (!p.ex || !p.e_mean || !p.e_rstd || !p.e_gamma || !p.e_beta)) return hipErrorInvalidValue;
     if (p.epi == EPI_RELUMASK && !p.ex) return hipErrorInvalidValue;
-    if (p.pro == PRO_POOLUP) return hipErrorInvalidValue;        // conv_poolup.hip
     const bool poolf = p.pro == PRO_BNRELU_POOL;
     if (poolf && (p.h % 2 || p.w % 2 || (int64_t)p.n * p.h * p.w != 4 * p.m || p.wtrans ||
                   (p.epi != EPI_STORE && p.epi != EPI_STATS) || p.accumulate || !p.p_mean || !p.p_gamma ||
@@ -702,14 +712,6 @@ hipError_t launch_conv1x1(const RowsParams &p, hipStream_t s, int64_t *rows)
     if (save && (p.wtrans || (p.epi != EPI_STORE && p.epi != EPI_STATS) || p.accumulate)) return hipErrorInvalidValue;
     if (p.side && !bnadd && !save) return hipErrorInvalidValue;
     if (p.e_zsrc && (p.epi != EPI_BNBWD || !p.ex2)) return hipErrorInvalidValue;
-    // 32-bit pixel indices and raw-buffer operand views: every span below 2^31 bytes
-    const int64_t lim = (int64_t)1 << 31;
-    const int64_t arows = poolf ? 4 * p.m : p.m;
-    if ((bnadd || save) && (p.m * p.side_ldc + p.K) * 2 >= lim) return hipErrorInvalidValue;
-    if (p.ex2 && (p.m * p.ex2_ldc + p.N) * 2 >= lim) return hipErrorInvalidValue;
-    if (p.m < 1 || arows >= (lim >> 1) || (arows * p.a_ldc + p.K) * 2 >= lim || (p.m * p.y_ldc + p.N) * 2 >= lim ||
-        (p.a2 && (p.m * p.a2_ldc + p.K) * 2 >= lim) || (p.ex && (p.m * p.ex_ldc + p.N) * 2 >= lim))
-        return hipErrorInvalidValue;
     const int ncol = p1_group_cols(p.K, p.N);
     P1Geom g = p1_geom(p.K, ncol, p.epi == EPI_BNBWD);
     g.ncg = (int)ceil_div(p.N, ncol);

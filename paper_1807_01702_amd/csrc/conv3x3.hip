@@ -703,10 +703,21 @@ __global__ __launch_bounds__(kP3Threads) void k_conv3x3(RowsParams p, P3Geom g)
 }
 
 // ------------------------------------------------------------- launchers ---
-bool conv3x3_supported(int dtype, int K, int N, int H, int W)
+// (operands past 32-bit offsets and the summed-gradient epilogue: conv_rows)
+bool conv3x3_supported(const RowsParams &p)
 {
-    if (dtype != DT_BF16 || K > 128 || N > 128 || W > kP3MaxW || W < 1 || H > kP3MaxH || H < 1) return false;
-    const P3Geom g = p3_geom(K, N, W);
+    if (p.dtype != DT_BF16 || p.taps != 9 || p.pro == PRO_POOLUP || p.e_scale || p.K > 128 || p.N > 128 || p.w > kP3MaxW ||
+        p.w < 1 || p.h > kP3MaxH || p.h < 1)
+        return false;
+    // 32-bit pixel indices and positions, raw-buffer operand views: every span below 2^31 bytes
+    const int64_t lim = (int64_t)1 << 31;
+    const bool save = p.pro == PRO_BNRELU && p.side;
+    if (p.m >= (lim >> 1) || (int64_t)p.n * (p.h + 2) * (p.w + 2) >= (lim >> 1) || (p.m * p.a_ldc + p.K) * 2 >= lim ||
+        (p.m * p.y_ldc + p.N) * 2 >= lim || (p.a2 && (p.m * p.a2_ldc + p.K) * 2 >= lim) ||
+        (p.ex && (p.m * p.ex_ldc + p.N) * 2 >= lim) || (save && (p.m * p.side_ldc + p.K) * 2 >= lim) ||
+        (p.ex2 && (p.m * p.ex2_ldc + p.N) * 2 >= lim))
+        return false;
+    const P3Geom g = p3_geom(p.K, p.N, p.w);
     const int wk = g.KP / 32, wn = g.NP / 32;
     if (wk * wn > 4) return false;                 // every wave one K and one N slice, at least two row groups
     return g.lds <= 160 * 1024;
@@ -785,14 +796,12 @@ static hipError_t run_p3_ek(const RowsParams &p, const P3Geom &g, int ek, hipStr
 
 hipError_t launch_conv3x3(const RowsParams &p, hipStream_t s)
 {
-    if (!p.a || !p.wraw || !p.y || p.taps != 9 || p.pro == PRO_POOLUP || !conv3x3_supported(p.dtype, p.K, p.N, p.h, p.w))
-        return hipErrorInvalidValue;
+    if (!p.a || !p.wraw || !p.y || !conv3x3_supported(p)) return hipErrorInvalidValue;
     if (p.pro == PRO_BNRELU && (!p.p_mean || !p.p_gamma || !p.p_rstd || !p.p_beta)) return hipErrorInvalidValue;
     if (p.pro == PRO_BNGRAD && (!p.a2 || !p.p_mean || !p.p_rstd ||
                                 (p.p_split ? (!p.p_alpha || !p.p_betap) : (!p.p_gamma || !p.p_dbeta || !p.p_dgamma))))
         return hipErrorInvalidValue;
     if ((p.epi == EPI_STATS || p.epi == EPI_BNBWD) && !p.part) return hipErrorInvalidValue;
-    if (p.epi == EPI_BNBWD && p.e_scale) return hipErrorInvalidValue;     // summed-gradient form: conv_rows
     if (p.epi == EPI_BNBWD && (!p.ex || !p.e_mean || !p.e_rstd || !p.e_gamma || !p.e_beta)) return hipErrorInvalidValue;
     if (p.epi == EPI_RELUMASK && !p.ex) return hipErrorInvalidValue;
     if ((int64_t)p.n * p.h * p.w != p.m || p.m < 1) return hipErrorInvalidValue;
@@ -800,12 +809,6 @@ hipError_t launch_conv3x3(const RowsParams &p, hipStream_t s)
     if (p.side && (!save || p.wtrans || (p.epi != EPI_STORE && p.epi != EPI_STATS) || p.accumulate))
         return hipErrorInvalidValue;
     if (p.e_zsrc && (p.epi != EPI_BNBWD || !p.ex2)) return hipErrorInvalidValue;
-    // 32-bit pixel indices and raw-buffer operand views: every span below 2^31 bytes
-    const int64_t lim = (int64_t)1 << 31;
-    if (p.m >= (lim >> 1) || (p.m * p.a_ldc + p.K) * 2 >= lim || (p.m * p.y_ldc + p.N) * 2 >= lim ||
-        (p.a2 && (p.m * p.a2_ldc + p.K) * 2 >= lim) || (p.ex && (p.m * p.ex_ldc + p.N) * 2 >= lim) ||
-        (save && (p.m * p.side_ldc + p.K) * 2 >= lim) || (p.ex2 && (p.m * p.ex2_ldc + p.N) * 2 >= lim))
-        return hipErrorInvalidValue;
     P3Geom g = p3_geom(p.K, p.N, p.w);
     g.PH = p.h + 2;
     const auto advance = [&](int positions) {
@@ -819,9 +822,7 @@ hipError_t launch_conv3x3(const RowsParams &p, hipStream_t s)
     const int tr = p3_tile_rows(g.KP / 32, g.NP / 32);
     g.ring_adv = advance(tr);
     g.epi_adv = advance(kP3Threads / (g.NP / 8) > tr ? 2 * tr : tr);      // (k_conv3x3: ALT)
-    const int64_t mp = (int64_t)p.n * g.PH * g.PW;                // padded positions
-    if (mp >= (lim >> 1)) return hipErrorInvalidValue;
-    g.MP = (int)mp;
+    g.MP = (int)((int64_t)p.n * g.PH * g.PW);                     // padded positions
     const int ek = epilogue_kind(p.epi, p.accumulate, 0);
     if (save) return ek == EK_STATS ? run_p3_shape<EK_STATS, PC3_BNRELU_SAVE>(p, g, s)
                                     : run_p3_shape<EK_STORE, PC3_BNRELU_SAVE>(p, g, s);

@@ -148,12 +148,12 @@ hipError_t launch_conv_rows(const RowsParams &p, hipStream_t s);
 int device_cus();             // compute units of the current device (256 without one)
 
 // ---- persistent 1x1 CONV (weights resident in LDS, one workgroup per CU) ----
-bool conv1x1_supported(int dtype, int K, int N, int epi);
+bool conv1x1_supported(const RowsParams &p);
 int64_t conv1x1_partial_rows(int64_t m);      // upper bound of the statistics partial rows it writes
 hipError_t launch_conv1x1(const RowsParams &p, hipStream_t s, int64_t *rows);   // *rows: partial rows written
 
 // ---- persistent 3x3 CONV (weights and an input-row ring buffer in LDS) ----
-bool conv3x3_supported(int dtype, int K, int N, int H, int W);
+bool conv3x3_supported(const RowsParams &p);
 int64_t conv3x3_partial_rows(int64_t m);      // statistics partial rows it writes
 hipError_t launch_conv3x3(const RowsParams &p, hipStream_t s);
 

@@ -25,8 +25,22 @@ def B():
     return bnr
 
 
-def _layer(B, bf16, k, n, h, w, ci, co, seed=11, pad_in=0, pad_out=0):
-    """Runs the layer both ways on views of wider buffers; returns nothing, asserts."""
+def _wide(t):
+    """t as a view whose pixel stride makes it span more than 2^31 bytes (what lies between is never written)."""
+    m, c = t.numel() // t.shape[-1], t.shape[-1]
+    vec = 16 // t.element_size()
+    ldc = ((1 << 31) // (t.element_size() * (m - 1)) // vec + 1) * vec
+    v = torch.empty((m - 1) * ldc + c, dtype=t.dtype, device=t.device).as_strided((m, c), (ldc, 1))
+    v.copy_(t.reshape(m, c))
+    shape, stride = t.shape[:-1], [ldc]
+    for s in reversed(shape[1:]):
+        stride.insert(0, stride[0] * s)
+    return v.as_strided(t.shape, (*stride, 1))
+
+
+def _layer(B, bf16, k, n, h, w, ci, co, seed=11, pad_in=0, pad_out=0, wide=False):
+    """Runs the layer both ways on views of wider buffers (wide: an input that
+    spans more than 2^31 bytes); returns nothing, asserts."""
     rnd = bf16_round if bf16 else (lambda a: np.asarray(a, np.float64))
     rtol, m = RTOL[bf16], n * h * w
     xf = synth.normal(seed, "x", (n, h, w, ci + pad_in), bf16=bf16)
@@ -37,6 +51,8 @@ def _layer(B, bf16, k, n, h, w, ci, co, seed=11, pad_in=0, pad_out=0):
     z = rnd(P.relu_fwd(y1).reshape(n, h, w, ci))
     out_r = rnd(P.conv_fwd(z, wt.astype(np.float64)))
     x = dev(xf, bf16)[..., :ci]
+    if wide:
+        x = _wide(x)
     wd = dev(wt, bf16)
     buf = torch.full((n, h, w, co + pad_out), 7.0, dtype=x.dtype, device=x.device)
     out = buf[..., :co]
@@ -166,6 +182,72 @@ def test_conv3x3_long_ranges_equal_short_ones(B, n, h, w, ci, co):
     for i in (0, 1, n // 3, n // 2, n - 2, n - 1):
         for name, t in forms(slice(i, i + 1)).items():
             assert torch.equal(whole[name][i], t[0]), "%s, image %d" % (name, i)
+
+
+# The kernels with 32-bit offsets leave operands of 2 GiB and more to the general
+# ones; a wide pixel stride reaches those with little work.
+@pytest.mark.parametrize("bf16,k,n,h,w,ci,co", [
+    (False, 1, 3, 7, 9, 36, 20),
+    (False, 1, 2, 9, 11, 140, 68),
+    (False, 3, 2, 5, 6, 12, 20),
+    (False, 3, 3, 7, 6, 40, 72),
+    (True, 1, 2, 9, 11, 64, 40),
+    (True, 1, 1, 9, 13, 264, 72),
+    (True, 3, 2, 6, 7, 96, 24),         # three K slices
+    (True, 3, 3, 5, 6, 128, 32),
+    (True, 3, 2, 9, 7, 40, 136),
+])
+def test_layer_on_an_input_past_2_gib(B, bf16, k, n, h, w, ci, co):
+    _layer(B, bf16, k, n, h, w, ci, co, pad_out=8, wide=True)
+
+
+@pytest.mark.parametrize("bf16,ci,co", [(False, 36, 20), (False, 72, 68), (True, 64, 40), (True, 264, 72)])
+def test_forms_on_an_input_past_2_gib(B, bf16, ci, co):
+    """The 1x1 CONV's other forms give on an input past 2 GiB what they give on
+    the same values close together."""
+    n, h, w, rtol = 2, 6, 10, RTOL[bf16]
+    x = dev(synth.normal(8, "x", (n, h, w, ci), bf16=bf16), bf16)
+    ident = dev(synth.normal(8, "id", (n, h, w, ci), bf16=bf16), bf16)
+    g, gp = (dev(synth.normal(8, s, (n, h // d, w // d, co), bf16=bf16), bf16) for s, d in (("g", 1), ("gp", 2)))
+    wt = dev(synth.conv_weight(8, "w", 1, ci, co, bf16), bf16)
+    p1 = synth.bn_params(8, "bn", ci)
+    gam = f32dev(p1["gamma"])
+    gam[ci // 2] = 0.0                                      # its vector reads x in the z form
+    bn = lambda: B.BN(gam, f32dev(p1["beta"]), 1e-5, f32dev(np.full(ci, 0.05)), f32dev(np.ones(ci)), f32dev(np.full(ci, 1.1)))
+
+    def run(xv):
+        new = lambda c, d=1: torch.empty((n, h // d, w // d, c), dtype=x.dtype, device="cuda")
+        o, f32 = {}, lambda *s: torch.empty(s, device="cuda")
+        desc = B.desc_for(xv, g, 1, n, h, w)
+        o["pooled"], st = new(co, 2), B.BN.stats_only(co, x.device)
+        B.bnr_bn_relu_conv_pool_fwd(desc, xv, bn(), wt, o["pooled"], st)
+        o["pooled mean"], o["pooled var"] = st.mean, st.var
+        o["r"], o["sum out"] = new(ci), new(co)
+        B.bnr_bn_add_relu_conv_fwd(desc, xv, bn(), ident, o["r"], wt, o["sum out"], B.BN.stats_only(co, x.device))
+        o["z"], o["z out"] = new(ci), new(co)
+        B.bnr_bn_relu_conv_fwd_o2(desc, xv, bn(), wt, o["z out"], o["z"], B.BN.stats_only(co, x.device))
+        for name, src in (("dense", B.grad_dense(g)), ("pooled gradient", B.grad_avgpool2(gp))):
+            dw = o[name + " dw"] = f32(1, 1, ci, co)
+            for form in ("dy", "z dy", "split", "split add", "dx", "dx add"):
+                y = o[name + " " + form] = torch.full((n, h, w, ci), 0.5, dtype=x.dtype, device="cuda")
+                dg, db, al, be = (torch.full((ci,), 0.5, device="cuda") for _ in range(4))
+                if form == "dy":
+                    B.bnr_bwd_fused(desc, xv, bn(), wt, src, dw, dg, db, y)
+                elif form == "z dy":
+                    B.bnr_bwd_fused_o2(desc, xv, bn(), o["z"], wt, src, f32(1, 1, ci, co), dg, db, y)
+                elif form.startswith("split"):
+                    B.bnr_bwd_fused_split(desc, xv, bn(), wt, src, f32(1, 1, ci, co), dg, db, y, al, be, accumulate=form == "split add")
+                    o[name + " " + form + " alpha"], o[name + " " + form + " betap"] = al, be
+                else:
+                    B.bnr_bwd_fused(desc, xv, None, wt, src, f32(1, 1, ci, co), dx=y, dx_accumulate=form == "dx add")
+                if not form.startswith("dx"):
+                    o[name + " " + form + " dgamma"], o[name + " " + form + " dbeta"] = dg, db
+        torch.cuda.synchronize()
+        return o
+
+    near, far = run(x), run(_wide(x))
+    for name in near:
+        assert_close(name, host(far[name]), host(near[name]), rtol)
 
 
 @pytest.mark.parametrize("k,n,h,w,ci,co", [
