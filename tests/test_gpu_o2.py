@@ -24,7 +24,7 @@ def B():
 
 CASES = [
     # bf16, k, n, h, w, c_in, c_out
-    (False, 1, 8, 8, 8, 64, 32),          # float32: tiled kernel
+    (False, 1, 8, 8, 8, 64, 32),          # float32
     (False, 3, 2, 5, 6, 12, 20),          # float32 3x3, ragged
     (True, 1, 2, 14, 14, 256, 128),       # persistent 1x1
     (True, 1, 1, 9, 11, 40, 136),         # persistent 1x1, ragged channels and pixels

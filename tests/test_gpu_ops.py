@@ -173,7 +173,7 @@ def test_conv_fwd(B, case, mode):
     (True, 4, 56, 56, 256, 128, 256, 128),      # dense block 1's transition (persistent 1x1 kernel)
     (True, 2, 6, 10, 200, 64, 208, 96),         # ragged channels, output view of a wider buffer
     (True, 2, 14, 14, 512, 256, 512, 512),      # K > 256: tiled kernel (DenseNet-121 transition 2 shape)
-    (False, 2, 4, 6, 40, 24, 48, 32),           # fp32 (tiled kernel)
+    (False, 2, 4, 6, 40, 24, 48, 32),           # fp32
 ])
 @pytest.mark.parametrize("stats", [False, True])
 def test_bn_relu_conv_pool_fwd(B, case, stats):
@@ -208,7 +208,7 @@ def test_bn_relu_conv_pool_fwd(B, case, stats):
     # dtype, n, h, w, c (y, identity, r), c_out, r_ldc
     (True, 2, 14, 14, 256, 64, 256),        # ResNet-50 conv2_x block boundary (persistent 1x1 kernel)
     (True, 1, 9, 11, 136, 40, 144),         # ragged pixels and channels, r into a wider view
-    (False, 2, 5, 6, 24, 16, 24),           # fp32 (tiled kernel)
+    (False, 2, 5, 6, 24, 16, 24),           # fp32
 ])
 def test_bn_add_relu_conv_fwd(B, case):
     """r = relu(bn(y) + identity) formed while the next block's first CONV
