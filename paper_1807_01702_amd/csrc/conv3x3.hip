@@ -60,8 +60,8 @@
 namespace bnr {
 
 constexpr int kP3Threads = 512;
-constexpr int kP3MaxW = 61;         // widest image row (2 (W + 3) halo rows in kP3Fill batches less one tile)
-constexpr int kP3MaxH = 896;        // tallest image
+constexpr int kP3MaxW = 61;         // widest image row (a tile and its 2 (W + 3) halo rows in p3_fill batches)
+constexpr int kP3MaxH = 896;        // tallest image that has been run (nothing below depends on it)
 
 // Rows of a tile with wk x wn channel slices (every wave has at least 16), the
 // ring batches (of one tile's rows) that cover a tile's window, the ring rows

@@ -276,11 +276,11 @@ __global__ __launch_bounds__(kThreads, BM == 64 && EK == EK_BNBWD_SCACC ? 2 : 3)
 }
 
 // ------------------------------------------------------------- launchers ---
-// Windows per tile: 64, or 32 while 64 would leave the chip's 256 CUs without
-// two workgroups each (a smaller tile stages the weights for half the rows).
+// Windows per tile: 64, or 32 while 64 would leave the chip's compute units
+// without two workgroups each (a smaller tile stages the weights for half the rows).
 static int pu_bm(int64_t m, int N)
 {
-    return ceil_div(m / 4, 64) * ceil_div(N, kPuBN) < 512 ? 32 : 64;
+    return ceil_div(m / 4, 64) * ceil_div(N, kPuBN) < 2 * device_cus() ? 32 : 64;
 }
 
 bool conv_poolup_supported(const RowsParams &p)

@@ -595,8 +595,9 @@ __global__ __launch_bounds__(kThreads, (TAPS == 3 && COT == 64) ? 1 : 2) void k_
 // row-major as they arrive, after the prologue transform, the nine taps of a
 // 3x3 row offsets into the staged Z.  A 16x16x4 float32 fragment takes one
 // value per lane (channel lane % 16, position lane / 16), a plain 4-byte read
-// of a row-major tile; row pitches of 16 mod 64 floats put the four rows of a
-// read on different banks.  The next chunk is loaded to registers during the
+// of a row-major tile; row pitches of 16 mod 32 floats put neighbouring rows of
+// a read on different halves of 32 banks (48 for 32-channel tiles: 16 mod 64 would
+// be a third more LDS).  The next chunk is loaded to registers during the
 // matrix-core work.  The matrix cores bound it; the transposed staging it
 // replaces wrote and read single floats and split a 3x3 by filter rows, so G
 // was staged three times.
