@@ -45,9 +45,9 @@
 // position decode per row and a ring wrap per fragment took 840 instructions
 // per wave and phase pair, half of them scalar; the walkers (p3_step) and one
 // address per filter row leave about 350.  128 -> 32 channels forward on
-// 64 images of 56 x 56: 40.2 -> 31 us; its data gradient with the BN-backward
-// epilogue: 51 -> 39 us (HBM floor 23); 64 -> 64 channels, 128 images,
-// forward: 73 -> 52 us.  Slower: 768 threads (three waves per SIMD), 8-byte
+// 64 images of 56 x 56: 40.2 -> 32 us; its data gradient with the BN-backward
+// epilogue: 51 -> 44 us (HBM floor 23); 64 -> 64 channels, 128 images,
+// forward: 73 -> 50 us (averages of a kernel trace).  Slower: 768 threads (three waves per SIMD), 8-byte
 // vectors so that every wave holds rows of each part, all three parts in one
 // basic block with the matrix-core work interleaved (34.6, 36, 36-39 us
 // against 33.5, by HIP events).

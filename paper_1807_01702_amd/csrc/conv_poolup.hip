@@ -323,7 +323,7 @@ hipError_t launch_conv_poolup(const RowsParams &p, hipStream_t s)
     double by = m / 4.0 * p.K + m * p.N + (double)p.K * p.N;
     if (p.epi == EPI_BNBWD) by += m * p.N;
     if (p.accumulate) by += m * p.N;
-    TraceScope tr(KC_CONV, KID_CONV_1X1, s, 2.0 * by, 2.0 * m * p.K * p.N);
+    TraceScope tr(KC_CONV, KID_CONV_1X1, s, 2.0 * by, 2.0 * (m / 4.0) * p.K * p.N);
     if (bm == 32) run_poolup<32>(p, ntiles, (unsigned)blocks, s);
     else run_poolup<64>(p, ntiles, (unsigned)blocks, s);
     return hipGetLastError();
